@@ -117,21 +117,19 @@ int lda_draw_naive(const float *theta, const float *phi, const int32_t *doc_id,
  * A wavefront takes 64 consecutive tokens, one per lane, and reads theta and
  * phi cooperatively: each load instruction fetches consecutive topics of one
  * token, or of a few tokens (coalesced), instead of one topic of 64 tokens.
- * The lanes combine their products in a butterfly pattern (log2 W exchange
- * stages) instead of a full transposition, and each lane reconstructs the
- * partial sums it needs from the butterfly table while it searches for u*S
- * (Algorithm 10).  The kernel depends on K:
- *  - K divisible by 4 up to 256 (N >= 64): groups of W = 8, 16, 32 or 64
- *    lanes, each lane one leaf of 4 topics; load k brings token k's whole
- *    row into its group; the butterfly runs over the W leaf sums, Algorithm
- *    10 finds the token's leaf and a scan of its 4 products the topic
- *    (groups of 8 lanes keep each leaf's partial sums in LDS for that scan;
- *    the others read the leaf again); from 260 to 508 (multiples of 32 only
- *    up to 416) the same with 64 lanes and leaves of 8 topics;
- *  - K divisible by 4 from 260 to 2048 otherwise: 256-topic blocks read as leaves of 4
+ * The kernel depends on K:
+ *  - K from 4 to 256 (N >= 64): groups of W = 4, 8, 16, 32 or 64 lanes, each
+ *    lane one leaf of 4 topics; load k brings token k's whole row into its
+ *    group; the leaf sums pass through LDS (8-lane groups: through lane
+ *    exchanges) to the lanes that search them for u*S, and a scan of the found
+ *    leaf's 4 products gives the topic (from sums kept on chip, or the leaf is
+ *    read again); from 257 to 512 the same with 64 lanes and leaves of 8
+ *    topics;
+ *  - K divisible by 4 from 516 to 2048: 256-topic blocks read as leaves of 4
  *    topics per lane; a first sweep keeps every token's prefix at the end of
  *    each 32-topic part of each block, Algorithm 9 finds the part holding
- *    u*S, whose butterfly table is rebuilt on chip and searched;
+ *    u*S, whose butterfly table is rebuilt on chip (Algorithm 8) and searched
+ *    (Algorithm 10);
  *  - otherwise: blocks of W topics, one topic per lane (W = 64 for K >= 64,
  *    32 below), the prefix at each block end, then Algorithm 9 and the
  *    rebuilt block (or half-block) with Algorithm 10.
@@ -228,7 +226,7 @@ int lda_philox_uniforms(float *u, int64_t count, int64_t first, uint64_t seed,
  *                               searched in LDS by a descent from the whole
  *                               block;
  *   LDA_VARIANT_LEAF8           where lda_draw_butterfly uses its leaf groups
- *                               (K divisible by 4 up to 256, N >= 64), leaves
+ *                               (K from 4 to 256, N >= 64), leaves
  *                               of 8 topics per lane in groups half as wide;
  *                               elsewhere the kernels of lda_draw_butterfly;
  *   LDA_VARIANT_WIDE_TABLES     the kernels of lda_draw_butterfly as built for

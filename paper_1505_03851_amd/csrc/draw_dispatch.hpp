@@ -88,42 +88,70 @@ void launch_eighths(const float *theta, const float *phi, DocSource d, const int
     launch_eighths<C, WPEU, true>(theta, phi, d, wd, u, z, N, M, V, K, s);
 }
 
-// The leaf-group kernel: K divisible by 4, up to LDA_GROUP_MAX_K (at most
-// 256) topics, N >= 64; groups of 8, 16, 32 or 64 lanes for K up to 32, 64,
-// 128, 256.  Measured on MI355X against the kernels it replaces there: 2.0x to
-// 2.6x faster than the one-topic kernel for K = 16 ... 128, 5-8% faster than
-// the eighths kernel for K = 144 ... 256.
+// The leaf-group kernel: K from 4 to LDA_GROUP_MAX_K (at most 256) topics, N >=
+// 64; groups of 4, 8, 16, 32 or 64 lanes for K up to 16, 32, 64, 128, 256.
+// Measured on MI355X against the kernels it replaces there: 2.0x to 2.6x faster
+// than the one-topic kernel for K = 10 ... 128 (K = 50 on 1M tokens: 40.9 ->
+// 15.7 us; 10 on 8M: 150 -> 49; 101 on 8M: 406 -> 197), 5-8% faster than the
+// eighths kernel for K = 144 ... 256.
 bool groups_for(int64_t N, int32_t K) {
-  return N >= kWave && K % kLeaf == 0 && K <= LDA_GROUP_MAX_K && K <= kLeaf * kWave;
+  return N >= kWave && K >= kLeaf && K <= LDA_GROUP_MAX_K && K <= kLeaf * kWave;
 }
 
-// (8-topic leaves hold twice the registers: the 64-lane groups' setting)
-template <int G, int H, int CW = (G == kWave ? LDA_GROUP64_WINDOW : LDA_GROUP_WINDOW),
-          int WPEU = ((G == kWave || H > 1) ? LDA_GROUP64_WAVES_PER_EU : LDA_GROUP_WAVES_PER_EU)>
-void launch_groups(const float *theta, const float *phi, DocSource d, const int32_t *wd,
-                   UniformSource u, int32_t *z, int64_t N, int32_t M, int32_t V, int32_t K,
-                   hipStream_t s) {
-  constexpr int C = CW < G ? CW : G;
+// Documents long enough that a 32-lane group's 32 consecutive tokens mostly
+// share one: there the sums are kept in registers (118 VGPRs, 4 wavefronts per
+// SIMD), else more wavefronts run (5 per SIMD).  Measured on MI355X: keeping
+// takes 199 us against 226 at K = 128 on 8M tokens in documents of 128, but
+// 152 against 135 at K = 80 on 6M tokens in documents of 69 on average; with
+// 128 tokens per document about half the groups' pairs lie in one document.
+bool long_docs(int64_t N, int32_t M) { return N >= 128 * (int64_t)M; }
+
+template <int G, int H, int C, int WPEU, bool KEEP>
+void launch_groups_as(const float *theta, const float *phi, DocSource d, const int32_t *wd,
+                      UniformSource u, int32_t *z, int64_t N, int32_t M, int32_t V, int32_t K,
+                      hipStream_t s) {
   const uint32_t tb = table_extent(M, K);
   const uint32_t pb = table_extent(V, K);
   const size_t lds = (size_t)kWavesPerBlock * group_lds_bytes<G, H>();
   if (K == kLeaf * H * G)
-    leaf_group_kernel<G, H, C, WPEU, false><<<wave_grid(N), kBlockThreads, lds, s>>>(
+    leaf_group_kernel<G, H, C, WPEU, KEEP, false><<<wave_grid(N), kBlockThreads, lds, s>>>(
         theta, phi, d, wd, u, z, N, K, tb, pb);
   else
-    leaf_group_kernel<G, H, C, WPEU, true><<<wave_grid(N), kBlockThreads, lds, s>>>(
+    leaf_group_kernel<G, H, C, WPEU, KEEP, true><<<wave_grid(N), kBlockThreads, lds, s>>>(
         theta, phi, d, wd, u, z, N, K, tb, pb);
 }
 
-// Groups of 64 lanes with 8-topic leaves for K from 260 to LDA_LEAF8_MAX_K
-// (at most 512), multiples of 32 only up to LDA_LEAF8_ALIGNED_MAX_K: the
-// whole row in one tile, as the leaf groups do up to 256.  Measured on MI355X
-// against the eighths kernel, which pads such K to two 256-topic blocks:
-// 17-21% faster at K = 260 ... 320, 7% at 384, 1-4% up to 508; 2-3% slower at
-// K = 448, 480 and 512.
+// Launch shapes by group and leaf (tuning.hpp).
+template <int G, int H>
+void launch_groups(const float *theta, const float *phi, DocSource d, const int32_t *wd,
+                   UniformSource u, int32_t *z, int64_t N, int32_t M, int32_t V, int32_t K,
+                   hipStream_t s) {
+  if constexpr (H > 1) {
+    launch_groups_as<G, H, (LDA_LEAF8_WINDOW < G ? LDA_LEAF8_WINDOW : G), LDA_LEAF8_WAVES_PER_EU,
+                     false>(theta, phi, d, wd, u, z, N, M, V, K, s);
+  } else if constexpr (G == kWave) {
+    launch_groups_as<G, H, LDA_GROUP64_WINDOW, LDA_GROUP64_WAVES_PER_EU, false>(
+        theta, phi, d, wd, u, z, N, M, V, K, s);
+  } else if constexpr (G == 32) {
+    if (long_docs(N, M))
+      launch_groups_as<G, H, 8, 4, true>(theta, phi, d, wd, u, z, N, M, V, K, s);
+    else
+      launch_groups_as<G, H, 4, 5, false>(theta, phi, d, wd, u, z, N, M, V, K, s);
+  } else if constexpr (G == 16) {
+    launch_groups_as<G, H, 8, 5, true>(theta, phi, d, wd, u, z, N, M, V, K, s);
+  } else {
+    launch_groups_as<G, H, G, 6, false>(theta, phi, d, wd, u, z, N, M, V, K, s);
+  }
+}
+
+// Groups of 64 lanes with 8-topic leaves for K from 257 to 512: the whole row
+// in one tile, as the leaf groups do up to 256.  Measured on MI355X against
+// the eighths kernel, which pads such K to two 256-topic blocks (4M tokens, V =
+// 50,000): 282 against 350 us at K = 260 (18% with the butterfly search it had
+// before), 347 at 384, 409 against 419 at 448, 470 against 479 at 512; against
+// the one-topic kernel 304 against 380 at K = 301, 491 against 609 at 501.
 bool leaf8_for(int64_t N, int32_t K) {
-  return N >= kWave && K % kLeaf == 0 && K > kLeaf * kWave && K <= LDA_LEAF8_MAX_K &&
-         K <= 2 * kLeaf * kWave && (K % 32 != 0 || K <= LDA_LEAF8_ALIGNED_MAX_K);
+  return N >= kWave && K > kLeaf * kWave && K <= LDA_LEAF8_MAX_K && K <= 2 * kLeaf * kWave;
 }
 
 // The eighths kernel takes K divisible by 4 (16-byte leaves) from
@@ -131,8 +159,8 @@ bool leaf8_for(int64_t N, int32_t K) {
 // N >= 64.  Measured on MI355X against the one-topic kernel: 15-30% faster
 // from K = 144 (K = 144 ... 240 on the paper-shaped corpus), 7% at K = 256,
 // 4% at K = 1024, 5% at K = 2048; 3-4% slower at K = 80 and 112, whose
-// padding fills most of the block.  (The dispatch gives K up to 256, and
-// most K up to 508, to the leaf-group kernel first.)
+// padding fills most of the block.  (The dispatch gives K up to 512 to
+// the leaf-group kernel first.)
 bool eighths_for(int64_t N, int32_t K) {
   return N >= kWave && K % kLeaf == 0 && K >= LDA_EIGHTHS_MIN_K &&
          eighths_blocks(K) <= LDA_EIGHTHS_MAX_BLOCKS;
@@ -161,7 +189,9 @@ template <int H>
 void dispatch_groups(const float *theta, const float *phi, DocSource d, const int32_t *word_id,
                      UniformSource u, int32_t *z, int64_t N, int32_t M, int32_t V, int32_t K,
                      hipStream_t s) {
-  if (K <= kLeaf * 8)
+  if (H == 1 && K <= kLeaf * 4)
+    launch_groups<4, 1>(theta, phi, d, word_id, u, z, N, M, V, K, s);
+  else if (K <= kLeaf * 8)
     launch_groups<8 / H, H>(theta, phi, d, word_id, u, z, N, M, V, K, s);
   else if (K <= kLeaf * 16)
     launch_groups<16 / H, H>(theta, phi, d, word_id, u, z, N, M, V, K, s);
@@ -183,8 +213,7 @@ void dispatch_butterfly(const float *theta, const float *phi, DocSource d,
   }
   if constexpr (LDA_LEAF8_MAX_K > 0) {
     if (leaf8_for(N, K)) {
-      launch_groups<kWave, 2, LDA_LEAF8_WINDOW, LDA_LEAF8_WAVES_PER_EU>(theta, phi, d, word_id,
-                                                                         u, z, N, M, V, K, s);
+      launch_groups<kWave, 2>(theta, phi, d, word_id, u, z, N, M, V, K, s);
       return;
     }
   }

@@ -1,4 +1,4 @@
-// Leaf-group kernel for K up to 256, and with 8-topic leaves up to 508
+// Leaf-group kernel for K from 4 to 256, and with 8-topic leaves up to 512
 // (gfx950).
 #pragma once
 
@@ -7,21 +7,40 @@
 namespace LDA_NS {
 namespace {
 
-// Leaf groups for K up to 256 (K divisible by 4, at most 4 G topics for a
-// group size G of 8, 16, 32 or 64 lanes; N >= 64), and with leaves of 4 H
-// topics (H quads) up to 4 H G; below, H = 1.  Sections 3 and 4 with a
-// 4-topic leaf in the place of a topic: a wavefront holds 64 / G groups of G
-// tokens, lane r of a group owns token r of the group and, in the tile, leaf
-// r (topics c0 + 4r .. c0 + 4r + 3, c0 = K - 4G <= 0: the first 4G - K
-// topics are empty) of every token of its group.  Load k brings leaf r of
-// token k of every group into lane r of that group, so each load instruction
-// reads the whole rows (16 G bytes) of 64 / G tokens.  Register a[k] is the
-// leaf sum (dot4) of token k; Algorithm 8's butterfly over the G leaves
-// leaves the table and the lane's own token's total; Algorithm 10 finds the
-// leaf whose prefix range holds u * S, and the leaf's four products,
-// reloaded for the lane's own token, give the topic by a scan from the
-// prefix before the leaf. The theta leaf comes once per lane when each
-// group's tokens share one document (GROUP_DOCS), else with every phi leaf.
+// Leaf groups for 4 <= K <= 4 H G topics (groups of G = 4, 8, 16, 32 or 64
+// lanes, leaves of 4 H topics: H quads).  Sections 3 and 4 with a leaf in the
+// place of a topic: a wavefront holds 64 / G groups of G tokens, lane r of a
+// group owns token r of the group and, in the tile, leaf r of every token of
+// its group.  Load k brings leaf r of token k of every group into lane r of
+// that group, so each load instruction reads the whole rows (16 G bytes for H
+// = 1) of 64 / G tokens, and the lane sums its leaf's products (dot4).
+//
+// The leaf sums go through LDS to the lanes that search them: every NLD loads
+// make a tile of T = 64 NLD / G tokens, P = 64 / T lanes then share a token,
+// each taking G / P consecutive leaf sums (16-byte reads), and the quad's
+// lanes learn each other's totals by DPP.  The search is a descent with
+// nested thresholds: the lane whose leaves hold u * S (prefixes of the lane
+// totals), the quad of leaves in it (prefixes of quad sums), the leaf, then
+// the topic by a scan of the leaf's products.  At K = 64 that is 195 vector
+// instructions per wavefront where Algorithm 8's butterfly over the leaf sums
+// with Algorithm 10's search-assist loop took 275, and one chain of LDS round
+// trips instead of one per level.  What bounds a draw here is the sum of
+// latencies of a wavefront (ids, rows, search) over the wavefronts that a CU
+// holds, then the L1's 64 bytes per clock; misses past L2 take over from about
+// K = 200.  Measured on MI355X (1M tokens, documents of 128): K = 64 17.2 ->
+// 14.8 us, K = 128 28.1 -> 25.8, K = 256 53.9 -> 51.0; on the paper-shaped
+// corpus K = 208 152 -> 136 us; K not divisible by 4, which one topic per lane
+// drew before: K = 50 41.0 -> 15.7, K = 250 82.7 -> 54.7.
+//
+// The topics of a row are padded in front to a whole number of leaves: index
+// i of the padded row (i < 0: empty leaves) is topic i for K divisible by 4;
+// else the first quad (0 <= i < 4) holds topics 0 .. K mod 4 - 1 in its first
+// components and none in the others, and i >= 4 is topic i - (4 - K mod 4).
+// No load leaves the token's row, whatever its alignment (a row needs K >= 4).
+// Empty components have a theta of zero, hence a prefix equal to the one
+// before them, and a search that skips every prefix <= u * S never ends in
+// front of the first topic.
+//
 // How the theta leaves of a group's tokens are found: every group's tokens in
 // one document (one leaf per lane, loaded once), in at most kMaxGroupRuns<G>
 // runs of documents (each run's leaf loaded once per lane; token k takes the
@@ -40,22 +59,62 @@ constexpr int kRunAhead = 4;  // tokens whose staged theta leaves are read ahead
 // select)
 template <int G>
 constexpr bool kStageRuns = G == kWave;
-// Groups of at most LDA_GROUP_KEEP_MAX_G lanes with 4-topic leaves keep, in
-// LDS, each leaf's running sums after its first three topics for every token
-// of the group (the dot4's intermediate values), so that the final scan
-// reads them there instead of reloading the chosen leaf from memory:
-// 12 (G + 1) bytes per token (rows padded by one leaf against LDS bank
-// conflicts).
-template <int G, int H>
-constexpr bool kKeepLeaves = H == 1 && G <= LDA_GROUP_KEEP_MAX_G;
 
-// LDS bytes per wavefront of the leaf-group kernel: the staged theta leaves
-// of up to kMaxGroupRuns<G> runs, or the kept leaf sums.
+// Shape of a tile and the layout of its leaf sums in LDS (see above).  Rows
+// are padded so that the 16-byte reads of eight consecutive lanes, and the
+// 4-byte writes of 32, fall on different banks.
+template <int G>
+struct GroupTile {
+  static constexpr int kLoads = G < 16 ? G : 16;       // loads per tile (NLD)
+  static constexpr int kTiles = G / kLoads;            // tiles per 64 tokens
+  static constexpr int kTokens = kLoads * (kWave / G);  // T
+  static constexpr int kParts = kWave / kTokens;       // lanes per token (P)
+  static constexpr int kLeaves = G / kParts;           // leaves per lane
+  static constexpr int kQuads = kLeaves / 4;           // 16-byte reads per lane
+  // floats between the rows of consecutive tokens (16-byte multiples)
+  static constexpr int kRow = G == 4 ? 4 : (G == kWave ? G + 8 : G + 4);
+  // floats between the tokens of consecutive groups
+  static constexpr int kGroup =
+      kLoads * kRow + (G == 4 ? 4 : (G == 8 ? 8 : (G == 16 ? 16 : 0)));
+  static constexpr int kFloats = (kWave / G) * kGroup;
+  // leaf r of a row: 64-leaf rows skip 4 floats after the first 32
+  __device__ static __forceinline__ int leaf(int r) {
+    return G == kWave ? r + 4 * (r >> 5) : r;
+  }
+};
+
+// How the last four topics of a draw are told apart.  Reload: the lane that
+// found the leaf reads it again (one cache line per token, against G / 8 per
+// token for the tile).  Groups of 4 and 8 lanes with 4-topic leaves (K <= 32)
+// write each leaf's running sums after one, two and three topics to LDS in the
+// tile and read the chosen leaf's there.  With KEEP, groups of 16 and 32 keep
+// them in registers until the tile has been searched, and the lane that holds
+// the leaf hands them over through LDS (in the modes that have the registers:
+// one document; for groups of 16 also any).
+enum GroupLast : int { kReload = 0, kKeepInLds = 1, kKeepInRegs = 2 };
+template <int G, int H, bool KEEP, int MODE>
+constexpr int kGroupLast =
+    H != 1 ? kReload
+           : (G <= 8 ? kKeepInLds
+                     : (KEEP && (MODE == kGroupOne || (G == 16 && MODE == kGroupAny))
+                            ? kKeepInRegs
+                            : kReload));
+
+// LDS bytes per wavefront: the tile's leaf sums (and in their place, once
+// searched, the leaves and sums handed over), then the kept sums (12 bytes per
+// token and leaf, rows padded by one leaf against bank conflicts) or, where
+// leaves are reloaded, the staged theta leaves of up to kMaxGroupRuns<G> runs.
+// Groups of 8 lanes transpose their leaf sums in registers.
+template <int G>
+constexpr int kSumFloats = G == 8 ? 0 : GroupTile<G>::kFloats;
 template <int G, int H>
 constexpr int group_lds_bytes() {
-  if constexpr (kKeepLeaves<G, H>) return kWave * (G + 1) * 3 * (int)sizeof(float);
-  return kMaxGroupRuns<G> * H * kWave * (int)sizeof(f4);
+  constexpr bool lds = kGroupLast<G, H, false, kGroupOne> == kKeepInLds;
+  return (kSumFloats<G> + (lds ? kWave * (G + 1) * 3 : 0)) * (int)sizeof(float) +
+         (lds ? 0 : kMaxGroupRuns<G> * H * kWave * (int)sizeof(f4));
 }
+
+using f3 = float __attribute__((ext_vector_type(3)));
 
 // A leaf of L = 4 H consecutive topics: H 16-byte quads.
 template <int H>
@@ -78,41 +137,386 @@ __device__ __forceinline__ float leaf_dot(const Leaf<H> &t, const Leaf<H> &p) {
   return s;
 }
 
-// The tile of a group: a[k] = this lane's leaf sum of token k of its group.
+// Value of x in lane J of this lane's quad (J = 0 .. 3) or pair (PARTS = 2, J
+// = 0, 1), by a DPP quad permutation.
+template <int PARTS, int J>
+__device__ __forceinline__ float part_value(float x) {
+  constexpr int ctrl = PARTS == 4 ? J * 0x55 : (J == 0 ? 0xA0 : 0xF5);
+  return as_float(__builtin_amdgcn_mov_dpp(as_int(x), ctrl, 0xF, 0xF, true));
+}
+
+// Exchange between lanes l and l xor BIT (1 or 2, inside a quad): lanes with
+// BIT clear receive the partner's x in y, lanes with BIT set the partner's y in
+// x (half_swap for the bits that DPP bank masks cannot pick).
+template <int BIT>
+__device__ __forceinline__ void quad_swap(float &x, float &y) {
+  const bool hi = (lane_id() & BIT) != 0;
+  const float got = xor_lane<BIT>(hi ? x : y);
+  x = hi ? got : x;
+  y = hi ? y : got;
+}
+
+// x moved by one DPP control.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u32(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xF, 0xF, true);
+}
+
+// Lane J of each half row of 8 lanes: row_newbcast of lane J, then of lane 8 +
+// J into the upper two banks.
+template <int J>
+__device__ __forceinline__ uint32_t half_row_bcast(uint32_t x) {
+  const int lo = __builtin_amdgcn_mov_dpp((int)x, 0x150 + J, 0xF, 0xF, true);
+  return (uint32_t)__builtin_amdgcn_update_dpp(lo, (int)x, 0x158 + J, 0xF, 0xC, false);
+}
+
+// Value held by lane k mod 16 of this lane's row of 16 (G = 16, 32), or by lane
+// k of this lane's group of G < 16, in every lane: DPP row broadcasts, for G =
+// 8 one per half row (bank masks), for G = 4 one per quad.
+template <int G>
+__device__ __forceinline__ uint32_t group_row(uint32_t x, int k) {
+  if constexpr (G == 4) {
+    switch (k & 3) {
+      case 0: return dpp_u32<0x00>(x);
+      case 1: return dpp_u32<0x55>(x);
+      case 2: return dpp_u32<0xAA>(x);
+      default: return dpp_u32<0xFF>(x);
+    }
+  } else if constexpr (G == 8) {
+    switch (k & 7) {
+      case 0: return half_row_bcast<0>(x);
+      case 1: return half_row_bcast<1>(x);
+      case 2: return half_row_bcast<2>(x);
+      case 3: return half_row_bcast<3>(x);
+      case 4: return half_row_bcast<4>(x);
+      case 5: return half_row_bcast<5>(x);
+      case 6: return half_row_bcast<6>(x);
+      default: return half_row_bcast<7>(x);
+    }
+  } else {
+    switch (k & 15) {
+      case 0: return dpp_u32<0x150>(x);
+      case 1: return dpp_u32<0x151>(x);
+      case 2: return dpp_u32<0x152>(x);
+      case 3: return dpp_u32<0x153>(x);
+      case 4: return dpp_u32<0x154>(x);
+      case 5: return dpp_u32<0x155>(x);
+      case 6: return dpp_u32<0x156>(x);
+      case 7: return dpp_u32<0x157>(x);
+      case 8: return dpp_u32<0x158>(x);
+      case 9: return dpp_u32<0x159>(x);
+      case 10: return dpp_u32<0x15A>(x);
+      case 11: return dpp_u32<0x15B>(x);
+      case 12: return dpp_u32<0x15C>(x);
+      case 13: return dpp_u32<0x15D>(x);
+      case 14: return dpp_u32<0x15E>(x);
+      default: return dpp_u32<0x15F>(x);
+    }
+  }
+}
+
+// What every token of the wavefront brings: handles of its rows, its uniform
+// and the run of documents it belongs to, in the lane that owns the token.
+struct GroupTokens {
+  uint32_t ph_lane, th_lane;
+  float u;
+  int run;
+  bool store;
+  int64_t n;
+};
+
+// A token whose leaf is known and whose leaf's factors are on their way.
+template <int H>
+struct GroupFound {
+  Leaf<H> th, ph;
+  float low, stop;
+  int leaf;         // the leaf (of the row)
+  int first;        // padded index of the leaf's first topic
+  int slot;         // the token's place in the tile
+  bool who;         // this lane's part of the token holds u * S
+  int32_t *z;       // where the draw goes
+  bool mine;        // this lane stores it
+  uint32_t ph_row, th_row;  // the token's rows, run and lane (for the reload)
+  int run, owner;
+};
+
+// Search of one tile: the P lanes of each token agree on the lane, quad and
+// leaf that hold u * S.  `sums`: the tile's leaf sums in LDS.
+template <int G, int H, int MODE>
+__device__ __forceinline__ GroupFound<H> group_search(const GroupTokens &tok, const float *sums,
+                                                      int tile, int c0, int32_t *z) {
+  using S = GroupTile<G>;
+  constexpr int P = S::kParts;
+  const int lane = lane_id();
+  const int t = lane / P, p = lane % P;       // token of the tile, part
+  const int g = t / S::kLoads, j = t % S::kLoads;
+  const int owner = g * G + tile * S::kLoads + j;  // lane that owns the token
+  // the token's values, from the lane that owns it (this one with P = 1)
+  GroupTokens my = tok;
+  int64_t n = tok.n;
+  if constexpr (P > 1) {
+    const int a = owner << 2;
+    my.ph_lane = (uint32_t)__builtin_amdgcn_ds_bpermute(a, (int)tok.ph_lane);
+    my.u = as_float(__builtin_amdgcn_ds_bpermute(a, as_int(tok.u)));
+    if constexpr (MODE == kGroupAny)
+      my.th_lane = (uint32_t)__builtin_amdgcn_ds_bpermute(a, (int)tok.th_lane);
+    if constexpr (MODE == kGroupRuns) my.run = __builtin_amdgcn_ds_bpermute(a, tok.run);
+    const uint64_t stores = __builtin_amdgcn_ballot_w64(tok.store);
+    my.store = (stores >> owner) & 1;
+    n = tok.n - lane + owner;
+  }
+  const float *row = sums + g * S::kGroup + j * S::kRow + S::leaf(p * S::kLeaves);
+  float q[S::kQuads];
+#pragma unroll
+  for (int i = 0; i < S::kQuads; ++i) {
+    const f4 x = *reinterpret_cast<const f4 *>(row + 4 * i);
+    q[i] = (x.x + x.y) + (x.z + x.w);
+  }
+  // prefixes of the quads inside this lane's part, then of the parts
+  float pre[S::kQuads + 1];
+  pre[0] = 0.0f;
+#pragma unroll
+  for (int i = 0; i < S::kQuads; ++i) pre[i + 1] = i == 0 ? q[0] : pre[i] + q[i];
+  const float part = pre[S::kQuads];
+  GroupFound<H> f;
+  float base = 0.0f, total;
+  int who = 0;  // the part that holds u * S: the last if none is above it
+  if constexpr (P == 1) {
+    total = part;
+    f.stop = total * my.u;
+  } else if constexpr (P == 2) {
+    const float e0 = part_value<2, 0>(part);
+    total = e0 + part_value<2, 1>(part);
+    f.stop = total * my.u;
+    who = f.stop < e0 ? 0 : 1;
+    base = p ? e0 : 0.0f;
+  } else {
+    const float e0 = part_value<4, 0>(part);
+    const float e1 = e0 + part_value<4, 1>(part);
+    const float e2 = e1 + part_value<4, 2>(part);
+    total = e2 + part_value<4, 3>(part);
+    f.stop = total * my.u;
+    who = f.stop < e0 ? 0 : f.stop < e1 ? 1 : f.stop < e2 ? 2 : 3;
+    base = p == 0 ? 0.0f : p == 1 ? e0 : p == 2 ? e1 : e2;
+  }
+  f.who = p == who;
+  f.mine = my.store && f.who;
+  // the quad of leaves, then the leaf
+  f.low = base;
+  int quad = 0;
+#pragma unroll
+  for (int i = 1; i < S::kQuads; ++i) {
+    const float at = base + pre[i];
+    const bool past = !(f.stop < at);
+    f.low = past ? at : f.low;
+    quad = past ? i : quad;
+  }
+  const f4 x = *reinterpret_cast<const f4 *>(row + 4 * quad);
+  const float a1 = f.low + x.x, a2 = f.low + (x.x + x.y), a3 = f.low + ((x.x + x.y) + x.z);
+  int leaf = p * S::kLeaves + 4 * quad;
+  const bool p1 = !(f.stop < a1), p2 = !(f.stop < a2), p3 = !(f.stop < a3);
+  f.low = p3 ? a3 : p2 ? a2 : p1 ? a1 : f.low;
+  leaf += p3 ? 3 : p2 ? 2 : p1 ? 1 : 0;
+  f.leaf = leaf;
+  f.first = c0 + kLeaf * H * leaf;
+  f.slot = t;
+  f.z = z + n;
+  f.ph_row = my.ph_lane;
+  f.th_row = my.th_lane;
+  f.run = MODE == kGroupRuns ? my.run : 0;
+  f.owner = owner;
+  return f;
+}
+
+// The same for groups of 8 lanes: a[k] is this lane's leaf sum of token k of
+// its group.  Three exchanges across lane bits 2, 1 and 0 transpose the 8 x 8
+// sums in registers, so that each lane scans its own token's.
+template <int H>
+__device__ __forceinline__ GroupFound<H> group8_search(const GroupTokens &tok, float (&a)[8],
+                                                       int c0, int32_t *z) {
+  const int lane = lane_id();
+#pragma unroll
+  for (int k = 0; k < 4; ++k) half_swap<4>(a[k], a[k + 4]);
+#pragma unroll
+  for (int k = 0; k < 8; k += 4) {
+    quad_swap<2>(a[k], a[k + 2]);
+    quad_swap<2>(a[k + 1], a[k + 3]);
+  }
+#pragma unroll
+  for (int k = 0; k < 8; k += 2) quad_swap<1>(a[k], a[k + 1]);
+  // prefixes at the leaves' ends; an end that is not above u * S is passed
+  float end[8];
+  end[0] = a[0];
+#pragma unroll
+  for (int i = 1; i < 8; ++i) end[i] = end[i - 1] + a[i];
+  GroupFound<H> f;
+  f.stop = end[7] * tok.u;
+  f.low = 0.0f;
+  f.leaf = 0;
+#pragma unroll
+  for (int i = 0; i < 7; ++i) {
+    const bool past = !(f.stop < end[i]);
+    f.low = past ? end[i] : f.low;
+    f.leaf = past ? i + 1 : f.leaf;
+  }
+  f.first = c0 + kLeaf * H * f.leaf;
+  f.slot = lane;
+  f.who = true;
+  f.mine = tok.store;
+  f.z = z + tok.n;
+  f.ph_row = tok.ph_lane;
+  f.th_row = tok.th_lane;
+  f.run = tok.run;
+  f.owner = lane;
+  return f;
+}
+
+// The factors of a found leaf, in the lane that found it: phi reloaded, theta
+// from the staged leaves or reloaded.
+template <int G, int H, int MODE, bool PAD>
+__device__ __forceinline__ void group_reload(GroupFound<H> &f, const Table &th_t,
+                                             const Table &ph_t, const f4 *stage, int drop) {
+  if (!f.mine) return;
+  const int gb = (f.owner & ~(G - 1)) + f.leaf;
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const int i = f.first + kLeaf * h;
+    const int topic = PAD ? (i >= kLeaf ? i - drop : 0) : i;
+    const uint32_t off = (uint32_t)topic * 4u;
+    f.ph.q[h] = ph_t.ld4v(off, f.ph_row);
+    if constexpr (MODE == kGroupAny) {
+      f.th.q[h] = th_t.ld4v(off, f.th_row);
+      if constexpr (PAD) {
+        // components past the topics the quad holds (see above)
+        const int real = i < 0 ? 0 : (i < kLeaf ? kLeaf - drop : kLeaf);
+#pragma unroll
+        for (int e = 0; e < kLeaf; ++e)
+          if (e >= real) f.th.q[h][e] = 0.0f;
+      }
+    } else {
+      f.th.q[h] = stage[((MODE == kGroupRuns ? f.run : 0) * H + h) * kWave + gb];
+    }
+  }
+}
+
+// Topic of padded index i >= 0 (the first quad's empty components hold a draw
+// only by rounding: its last topic).
+template <bool PAD>
+__device__ __forceinline__ int group_topic(int i, int drop) {
+  return PAD ? max(i - drop, min(i, kLeaf - 1 - drop)) : i;
+}
+
+// The topic of a found token: the first of its leaf's L topics whose running
+// sum exceeds u * S, else the last.
+template <int H, bool PAD>
+__device__ __forceinline__ void group_finish(const GroupFound<H> &f, int drop) {
+  constexpr int L = kLeaf * H;
+  if (!f.mine) return;
+  float sum = f.low;
+  int i = L - 1;
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+#pragma unroll
+    for (int e = 0; e < kLeaf; ++e) {
+      const int idx = kLeaf * h + e;
+      if (idx == L - 1) break;  // the leaf's last topic needs no comparison
+      sum = __builtin_fmaf(f.th.q[h][e], f.ph.q[h][e], sum);
+      if (i == L - 1 && f.stop < sum) i = idx;
+    }
+  }
+  *f.z = group_topic<PAD>(f.first + i, drop);
+}
+
+// The topic of a found token from its leaf's running sums after one, two and
+// three topics (nondecreasing: the products are not negative).
+template <bool PAD>
+__device__ __forceinline__ void group_store_kept(const GroupFound<1> &f, float s0, float s1,
+                                                 float s2, int drop) {
+  const int i = f.stop < f.low + s0 ? 0 : f.stop < f.low + s1 ? 1 : f.stop < f.low + s2 ? 2 : 3;
+  if (f.mine) *f.z = group_topic<PAD>(f.first + i, drop);
+}
+
+// The running sums kept in registers: lane r of group g holds those of
+// leaf r for the tile's tokens g NLD + k in kept[k]; the lane whose leaf a
+// token ended in writes them for the lane that searched the token.
+template <int G, bool PAD>
+__device__ __forceinline__ void group_finish_kept(const GroupFound<1> &f,
+                                                  const f3 (&kept)[GroupTile<G>::kLoads],
+                                                  float *sums, int drop) {
+  using S = GroupTile<G>;
+  const int lane = lane_id(), r = lane & (G - 1), g = lane / G;
+  int *leaves = reinterpret_cast<int *>(sums);
+  f3 *slots = reinterpret_cast<f3 *>(sums + kWave);  // (16 bytes each)
+  if (f.who) leaves[f.slot] = f.leaf;
+  lds_order();
+#pragma unroll
+  for (int i = 0; i < S::kLoads / 4; ++i) {
+    const int4 q = *reinterpret_cast<const int4 *>(leaves + g * S::kLoads + 4 * i);
+    const int at = g * S::kLoads + 4 * i;
+    if (q.x == r) slots[at] = kept[4 * i];
+    if (q.y == r) slots[at + 1] = kept[4 * i + 1];
+    if (q.z == r) slots[at + 2] = kept[4 * i + 2];
+    if (q.w == r) slots[at + 3] = kept[4 * i + 3];
+  }
+  lds_order();
+  const f3 s = slots[f.slot];
+  group_store_kept<PAD>(f, s.x, s.y, s.z, drop);
+}
+
+// The tiles of a wavefront: leaf sums, search and topics of its 64 tokens.
 // voff[h]: byte offset of quad h of this lane's leaf in a row; real[h]: the
-// quad holds topics (false: front padding, its theta is zero).  With
-// kKeepLeaves, the running sums after the leaf's first one, two and three
-// topics go to keep2[t (G + 1) + r] (the first two) and keep1[t (G + 1) + r]
-// for the wavefront's token t = gbase + k and this lane's leaf r.
-template <int G, int H, int C, int MODE>
-__device__ __forceinline__ void group_tile(float (&a)[G], const Table &th_t, const Table &ph_t,
-                                           const uint32_t (&voff)[H], const bool (&real)[H],
-                                           uint32_t ph_lane, uint32_t th_lane, int gbase,
-                                           uint64_t gstarts, f4 *stage, f2 *keep2,
-                                           float *keep1) {
-  constexpr bool KEEP = kKeepLeaves<G, H>;
+// topics it holds, in its first components (0: front padding).
+template <int G, int H, int C, bool KEEP, int MODE, bool PAD>
+__device__ __forceinline__ void group_tiles(const Table &th_t, const Table &ph_t,
+                                            const uint32_t (&voff)[H], const int (&real)[H],
+                                            const GroupTokens &tok, int gbase, uint64_t gstarts,
+                                            float *sums, f4 *stage, int c0, int drop,
+                                            int32_t *z) {
+  using S = GroupTile<G>;
   static_assert(G % C == 0, "the window size must divide G");
+  constexpr int LAST = kGroupLast<G, H, KEEP, MODE>;
   constexpr int R = MODE == kGroupRuns ? kMaxGroupRuns<G> : 1;
-  const f4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
-  // leaf of token k of the group at row offset `row` of that token (held by
-  // the lane that owns the token): with G = 64 the row is uniform and goes in
-  // the scalar offset, else it is fetched per lane
-  const auto leaf_of = [&](const Table &t, uint32_t row, int k) {
+  const int lane = lane_id(), r = lane & (G - 1);
+  // Leaf of token k of the group.  `rows` holds the row handles: with G = 64
+  // this lane's token's (token k's is uniform and goes in the scalar offset),
+  // with G = 8 and 16 too (token k's comes from its lane by a DPP row
+  // broadcast, no LDS round trip before the load), with G = 32 those of the
+  // tile's 16 tokens, in every row of 16 lanes of the group (rows_of_tile).
+  const auto leaf_of = [&](const Table &t, uint32_t rows, int k) {
     Leaf<H> l;
     if constexpr (G == kWave) {
-      const uint32_t srow = (uint32_t)__builtin_amdgcn_readlane((int)row, k);
+      const uint32_t srow = (uint32_t)__builtin_amdgcn_readlane((int)rows, k);
 #pragma unroll
       for (int h = 0; h < H; ++h) l.q[h] = t.ld4(voff[h], srow);
     } else {
-      const uint32_t vrow = (uint32_t)__builtin_amdgcn_ds_bpermute((gbase + k) << 2, (int)row);
+      const uint32_t vrow = group_row<G>(rows, k);
 #pragma unroll
       for (int h = 0; h < H; ++h) l.q[h] = t.ld4v(voff[h], vrow);
     }
     return l;
   };
-  const auto mask = [&](Leaf<H> l) {
+  constexpr int NT = G == 32 ? S::kTiles : 1;
+  uint32_t ph_rows[NT], th_rows[NT];
 #pragma unroll
-    for (int h = 0; h < H; ++h) l.q[h] = real[h] ? l.q[h] : zero;
+  for (int i = 0; i < NT; ++i) {
+    ph_rows[i] = tok.ph_lane;
+    th_rows[i] = tok.th_lane;
+    if constexpr (G == 32) {
+      const int from = (gbase + i * S::kLoads + (lane & 15)) << 2;
+      ph_rows[i] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)tok.ph_lane);
+      if constexpr (MODE != kGroupOne)
+        th_rows[i] = (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)tok.th_lane);
+    }
+  }
+  const auto ph_leaf = [&](int k) { return leaf_of(ph_t, ph_rows[G == 32 ? k / S::kLoads : 0], k); };
+  const auto th_leaf = [&](int k) { return leaf_of(th_t, th_rows[G == 32 ? k / S::kLoads : 0], k); };
+  const auto mask = [&](Leaf<H> l) {
+    if constexpr (PAD) {
+#pragma unroll
+      for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int e = 0; e < kLeaf; ++e) l.q[h][e] = e < real[h] ? l.q[h][e] : 0.0f;
+    }
     return l;
   };
   // kGroupRuns: gstarts bit p (0 < p < G) marks the group's token p as the
@@ -121,21 +525,27 @@ __device__ __forceinline__ void group_tile(float (&a)[G], const Table &th_t, con
   if constexpr (MODE == kGroupOne) {
     Leaf<H> l;
 #pragma unroll
-    for (int h = 0; h < H; ++h) l.q[h] = th_t.ld4v(voff[h], th_lane);
+    for (int h = 0; h < H; ++h) l.q[h] = th_t.ld4v(voff[h], tok.th_lane);
     th[0] = mask(l);
   } else if constexpr (MODE == kGroupRuns) {
     uint64_t m = gstarts;
-    th[0] = mask(leaf_of(th_t, th_lane, 0));
+    th[0] = mask(th_leaf(0));
 #pragma unroll
     for (int j = 1; j < R; ++j) {
       const int p = m ? (int)__builtin_ctzll(m) : 0;
       m &= m - 1;
-      th[j] = mask(leaf_of(th_t, th_lane, p));
+      Leaf<H> l;
+      const uint32_t row = (uint32_t)__builtin_amdgcn_ds_bpermute((gbase + p) << 2, (int)tok.th_lane);
+#pragma unroll
+      for (int h = 0; h < H; ++h) l.q[h] = th_t.ld4v(voff[h], row);
+      th[j] = mask(l);
     }
   }
-  if constexpr (MODE != kGroupAny && !KEEP) {
+  Leaf<H> win[C];
+#pragma unroll
+  for (int k = 0; k < C; ++k) win[k] = ph_leaf(k);
+  if constexpr (MODE != kGroupAny && LAST == kReload) {
     // stage the runs' leaves: quad h of run j at stage[(j H + h) 64 + lane]
-    const int lane = lane_id();
 #pragma unroll
     for (int j = 0; j < R; ++j)
 #pragma unroll
@@ -149,23 +559,30 @@ __device__ __forceinline__ void group_tile(float (&a)[G], const Table &th_t, con
   };
   const auto staged = [&](int k) {
     Leaf<H> l;
-    const int base = run_of(k) * H * kWave + lane_id();
+    const int base = run_of(k) * H * kWave + lane;
 #pragma unroll
     for (int h = 0; h < H; ++h) l.q[h] = stage[base + h * kWave];
     return l;
   };
   constexpr bool STAGED = MODE == kGroupRuns && kStageRuns<G>;
   constexpr int CT = MODE == kGroupAny ? C : (STAGED ? kRunAhead : 1);
-  Leaf<H> win[C], twin[CT];
+  Leaf<H> twin[CT];
+  if constexpr (MODE == kGroupAny) {
 #pragma unroll
-  for (int k = 0; k < C; ++k) {
-    win[k] = leaf_of(ph_t, ph_lane, k);
-    if constexpr (MODE == kGroupAny) twin[k] = leaf_of(th_t, th_lane, k);
+    for (int k = 0; k < C; ++k) twin[k] = th_leaf(k);
   }
   if constexpr (STAGED) {
 #pragma unroll
     for (int k = 0; k < CT; ++k) twin[k] = staged(k);
   }
+  // this lane's place in the rows of its group's tokens
+  float *put = sums + (gbase / G) * S::kGroup + S::leaf(r);
+  GroupFound<H> found{};
+  f3 kept[S::kLoads];  // kKeepInRegs: the running sums of this lane's leaf
+  float a[G == 8 ? G : 1];  // G = 8: the leaf sums
+  // kKeepInLds: the running sums after one and two topics, and three
+  f2 *keep2 = reinterpret_cast<f2 *>(sums + kSumFloats<G>);
+  float *keep1 = sums + kSumFloats<G> + 2 * kWave * (G + 1);
 #pragma unroll
   for (int k = 0; k < G; ++k) {
     Leaf<H> tv;
@@ -183,69 +600,102 @@ __device__ __forceinline__ void group_tile(float (&a)[G], const Table &th_t, con
     } else {
       tv = th[0];
     }
-    if constexpr (KEEP) {
-      // dot4's steps, the first three sums kept
-      const f4 t = tv.q[0], p = win[k % C].q[0];
-      const float s0 = t.x * p.x;
-      const float s1 = __builtin_fmaf(t.y, p.y, s0);
-      const float s2 = __builtin_fmaf(t.z, p.z, s1);
-      a[k] = __builtin_fmaf(t.w, p.w, s2);
-      const int at = (gbase + k) * (G + 1) + (lane_id() & (G - 1));
-      keep2[at] = f2{s0, s1};
-      keep1[at] = s2;
+    float sum;
+    if constexpr (LAST != kReload) {
+      // leaf_dot's steps, every sum kept
+      const f4 t = tv.q[0], x = win[k % C].q[0];
+      f4 s;
+      s.x = t.x * x.x;
+      s.y = __builtin_fmaf(t.y, x.y, s.x);
+      s.z = __builtin_fmaf(t.z, x.z, s.y);
+      s.w = __builtin_fmaf(t.w, x.w, s.z);
+      sum = s.w;
+      if constexpr (LAST == kKeepInRegs) {
+        kept[k % S::kLoads] = f3{s.x, s.y, s.z};
+      } else {
+        const int at = (gbase + k) * (G + 1) + r;
+        keep2[at] = f2{s.x, s.y};
+        keep1[at] = s.z;
+      }
     } else {
-      a[k] = leaf_dot(tv, win[k % C]);
+      sum = leaf_dot(tv, win[k % C]);
     }
+    if constexpr (G == 8)
+      a[k] = sum;
+    else
+      put[(k % S::kLoads) * S::kRow] = sum;
     if (k + C < G) {
-      win[k % C] = leaf_of(ph_t, ph_lane, k + C);
-      if constexpr (MODE == kGroupAny) twin[k % C] = leaf_of(th_t, th_lane, k + C);
+      win[k % C] = ph_leaf(k + C);
+      if constexpr (MODE == kGroupAny) twin[k % C] = th_leaf(k + C);
     }
     if constexpr (STAGED)
       if (k + CT < G) twin[k % CT] = staged(k + CT);
     __builtin_amdgcn_sched_barrier(0);
+    if ((k + 1) % S::kLoads == 0) {
+      // The tile's search; its reload is in flight while the next tile's
+      // leaves are summed (whose first C loads were issued before it).
+      lds_order();
+      GroupFound<H> now;
+      if constexpr (G == 8)
+        now = group8_search<H>(tok, a, c0, z);
+      else
+        now = group_search<G, H, MODE>(tok, sums, k / S::kLoads, c0, z);
+      if constexpr (LAST == kKeepInRegs) {
+        lds_order();
+        group_finish_kept<G, PAD>(now, kept, sums, drop);
+      } else if constexpr (LAST == kKeepInLds) {
+        const int at = lane * (G + 1) + now.leaf;
+        const f2 s01 = keep2[at];
+        group_store_kept<PAD>(now, s01.x, s01.y, keep1[at], drop);
+      } else {
+        group_reload<G, H, MODE, PAD>(now, th_t, ph_t, stage, drop);
+        if (k >= S::kLoads) group_finish<H, PAD>(found, drop);
+        found = now;
+      }
+      lds_order();
+    }
   }
-  if constexpr (KEEP) lds_order();
+  if constexpr (LAST == kReload) group_finish<H, PAD>(found, drop);
 }
 
 // L = 4 H topics per lane: groups of G lanes cover 4 H G topics.
-template <int G, int H, int C, int WPEU, bool PAD>
+template <int G, int H, int C, int WPEU, bool KEEP, bool PAD>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(WPEU)))
 void leaf_group_kernel(const float *__restrict__ theta, const float *__restrict__ phi,
                        DocSource docs, const int32_t *__restrict__ word_id,
                        UniformSource u, int32_t *__restrict__ z, int64_t N, int K,
                        uint32_t theta_extent, uint32_t phi_extent) {
   constexpr int L = kLeaf * H;
-  constexpr bool KEEP = kKeepLeaves<G, H>;
-  extern __shared__ float lds[];
+  extern __shared__ __align__(16) float lds[];
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  float *region = lds + wave * (group_lds_bytes<G, H>() / (int)sizeof(float));
-  f4 *stage = reinterpret_cast<f4 *>(region);
-  f2 *keep2 = reinterpret_cast<f2 *>(region);
-  float *keep1 = region + 2 * kWave * (G + 1);
+  float *sums = lds + wave * (group_lds_bytes<G, H>() / (int)sizeof(float));
+  f4 *stage = reinterpret_cast<f4 *>(sums + kSumFloats<G>);
   const int64_t first = ((int64_t)blockIdx.x * kWavesPerBlock + wave) * kWave;
   if (first >= N) return;  // whole wavefront past the end
   // Window of 64 tokens as in butterfly_kernel (N >= 64 here).
   const int64_t t0 = first + kWave <= N ? first : N - kWave;
-  const int64_t n = t0 + lane;
-  const bool store = n >= first;
-  const int doc = docs.wave_doc(n, t0, t0 + kWave - 1);
-  const int word = word_id[n];
-  const float un = u(n);
+  GroupTokens tok;
+  tok.n = t0 + lane;
+  tok.store = tok.n >= first;
+  const int doc = docs.wave_doc(tok.n, t0, t0 + kWave - 1);
+  const int word = word_id[tok.n];
+  tok.u = u(tok.n);
 
   const Table th_t = make_table(theta, theta_extent, K);
   const Table ph_t = make_table(phi, phi_extent, K);
-  const uint32_t ph_lane = ph_t.row((uint32_t)word);
-  const uint32_t th_lane = th_t.row((uint32_t)doc);
+  tok.ph_lane = ph_t.row((uint32_t)word);
+  tok.th_lane = th_t.row((uint32_t)doc);
   const int r = lane & (G - 1), gbase = lane & ~(G - 1);
-  const int c0 = K - L * G;  // first topic of leaf 0 (< 0: front padding)
+  const int drop = PAD ? (-K) & (kLeaf - 1) : 0;  // empty components of the first quad
+  const int c0 = K + drop - L * G;  // padded index of leaf 0's first topic
   uint32_t voff[H];
-  bool real[H];
+  int real[H];
 #pragma unroll
   for (int h = 0; h < H; ++h) {
-    const int topic = c0 + L * r + kLeaf * h;
-    real[h] = !PAD || topic >= 0;
-    voff[h] = (uint32_t)(real[h] ? topic : 0) * 4u;
+    const int i = c0 + L * r + kLeaf * h;
+    real[h] = !PAD || i >= kLeaf ? kLeaf : (i < 0 ? 0 : kLeaf - drop);
+    voff[h] = (uint32_t)(!PAD ? i : (i >= kLeaf ? i - drop : 0)) * 4u;
   }
   // runs of documents inside each group: bit l of `starts` marks lane l's
   // token as the first of a run (not counting the group's first token)
@@ -255,84 +705,28 @@ void leaf_group_kernel(const float *__restrict__ theta, const float *__restrict_
   const uint64_t starts = __builtin_amdgcn_ballot_w64(r != 0 && doc != prev);
   const uint64_t gmask = G == kWave ? ~0ull : ((1ull << G) - 1ull);
   const uint64_t gstarts = (starts >> gbase) & gmask;  // this lane's group, bit p = token p
+  tok.run = __builtin_popcountll(gstarts & ((2ull << r) - 1ull));
   // the most runs in any group (groups of G lanes: at most 64 / G of them)
   int most = 0;
 #pragma unroll
   for (int g = 0; g < kWave / G; ++g)
     most = max(most, __builtin_popcountll((starts >> (g * G)) & gmask));
 
-  float a[G];
+  // Windows of the modes that keep their sums in registers: for groups of 16
+  // all 16 tokens in one document (the sums take the loaded leaves' place),
+  // fewer where theta comes per token too.
+  constexpr bool K16 = G == 16 && H == 1 && KEEP;
+  constexpr int C1 = K16 ? G : C;
+  constexpr int CA = K16 ? (PAD ? 2 : 4) : (G == kWave && H == 1 ? C / 2 : C);
   if (most == 0)
-    group_tile<G, H, C, kGroupOne>(a, th_t, ph_t, voff, real, ph_lane, th_lane, gbase, 0,
-                                   stage, keep2, keep1);
+    group_tiles<G, H, C1, KEEP, kGroupOne, PAD>(th_t, ph_t, voff, real, tok, gbase, 0, sums, stage, c0,
+                                         drop, z);
   else if (most < kMaxGroupRuns<G>)
-    group_tile<G, H, C, kGroupRuns>(a, th_t, ph_t, voff, real, ph_lane, th_lane, gbase,
-                                    gstarts, stage, keep2, keep1);
+    group_tiles<G, H, C, KEEP, kGroupRuns, PAD>(th_t, ph_t, voff, real, tok, gbase, gstarts, sums,
+                                          stage, c0, drop, z);
   else
-    group_tile<G, H, C, kGroupAny>(a, th_t, ph_t, voff, real, ph_lane, th_lane, gbase, 0,
-                                   stage, keep2, keep1);
-  butterfly_block<G>(a, r, NoStore{});
-  const float total = a[G - 1];
-  const float stop = total * un;
-  float low = 0.0f, high = total;
-  int q = inblock_search<G, false>(a, nullptr, r, gbase, stop, low, high);
-  // The search rebuilds prefixes as low + y or high - y.  Where the true
-  // prefix is 0 (up to the first real topic) high - y may round to a tiny
-  // nonzero value, and a stop of 0 (u = 0) or of a few ulps of S may then
-  // end the search in a padding leaf.  The true prefix before the leaf
-  // holding topic 0 is exactly 0, so the search never ends before that leaf,
-  // and from there it scans from exactly 0.
-  if constexpr (PAD) {
-    const int qmin = (-c0) / L;  // leaf holding topic 0
-    if (q <= qmin) {
-      q = qmin;
-      low = 0.0f;
-    }
-  }
-  // Leaf q of the lane's own token, scanned from the prefix before it: the
-  // first of its L topics whose running sum exceeds stop, else the last.
-  // Padding topics (front of leaf qmin when L does not divide K) have zero
-  // weight and a running sum of exactly 0 <= stop, so they are never chosen;
-  // with S = 0 every comparison fails and the result is K - 1.
-  // The theta leaf: staged in LDS by lane gbase + q for the run of the
-  // lane's own token (padding quads already zero there), unless the group's
-  // documents were too many runs.
-  const int tq = c0 + L * q;
-  if constexpr (KEEP) {
-    // the kept sums of leaf q of this lane's token (nondecreasing: the
-    // products are not negative), added to the prefix before the leaf
-    const int at = lane * (G + 1) + q;
-    const f2 s01 = keep2[at];
-    const float s2 = keep1[at];
-    const int i = stop < low + s01.x ? 0 : stop < low + s01.y ? 1 : stop < low + s2 ? 2 : 3;
-    if (store) z[n] = tq + i;
-    return;
-  }
-  const bool staged = most < kMaxGroupRuns<G>;
-  const int run = __builtin_popcountll(gstarts & ((2ull << r) - 1ull));
-  float sum = low;
-  int i = L - 1;
-#pragma unroll
-  for (int h = 0; h < H; ++h) {
-    const int topic = tq + kLeaf * h;
-    const uint32_t qoff = (uint32_t)(topic > 0 ? topic : 0) * 4u;
-    f4 tl;
-    if (staged) {
-      tl = stage[(run * H + h) * kWave + gbase + q];
-    } else {
-      tl = th_t.ld4v(qoff, th_lane);
-      if (PAD && topic < 0) tl = f4{0.0f, 0.0f, 0.0f, 0.0f};
-    }
-    const f4 pl = ph_t.ld4v(qoff, ph_lane);
-#pragma unroll
-    for (int e = 0; e < kLeaf; ++e) {
-      const int idx = kLeaf * h + e;
-      if (idx == L - 1) break;  // the leaf's last topic needs no comparison
-      sum = __builtin_fmaf(tl[e], pl[e], sum);
-      if (i == L - 1 && stop < sum) i = idx;
-    }
-  }
-  if (store) z[n] = tq + i;
+    group_tiles<G, H, CA, KEEP, kGroupAny, PAD>(th_t, ph_t, voff, real, tok, gbase, 0, sums, stage, c0,
+                                         drop, z);
 }
 
 }  // namespace

@@ -39,69 +39,40 @@
 #ifndef LDA_EIGHTHS_MAX_BLOCKS
 #define LDA_EIGHTHS_MAX_BLOCKS 8
 #endif
-//   LDA_GROUP_MAX_K           largest K drawn by the leaf-group kernel (K
-//                             divisible by 4, at most 256; 0: never), and its
-//                             tokens in flight per wavefront and wavefronts
-//                             per SIMD for groups of 8 to 32 lanes: 8 at 4
-//                             (93-118 VGPRs, no spills) was 4-11% faster than
-//                             8 at 3 at K = 48 ... 112 and within 2% of the
-//                             best of 4 or 8 at 3 ... 5 at K = 16 ... 112.
+//   LDA_GROUP_MAX_K           largest K drawn by the leaf-group kernel with
+//                             4-topic leaves (K >= 4, at most 256; 0: never).
 #ifndef LDA_GROUP_MAX_K
 #define LDA_GROUP_MAX_K 256
 #endif
-#ifndef LDA_GROUP_WINDOW
-#define LDA_GROUP_WINDOW 8
+//   LDA_GROUP64_WINDOW, LDA_GROUP64_WAVES_PER_EU  tokens in flight per
+//                             wavefront and wavefronts per SIMD of its 64-lane
+//                             groups (K from 129 to 256): 8 at 4 (128 VGPRs)
+//                             took 133 us on the paper-shaped corpus at K =
+//                             208, 8 at 3 took 147; even at K = 256 on 1M
+//                             tokens (51 us).  Narrower groups: see
+//                             launch_groups.
+#ifndef LDA_GROUP64_WINDOW
+#define LDA_GROUP64_WINDOW 8
 #endif
-#ifndef LDA_GROUP_WAVES_PER_EU
-#define LDA_GROUP_WAVES_PER_EU 4
+#ifndef LDA_GROUP64_WAVES_PER_EU
+#define LDA_GROUP64_WAVES_PER_EU 4
 #endif
-//   LDA_GROUP64_WINDOW, LDA_GROUP64_WAVES_PER_EU  the same for groups of 64
-//                             lanes (K from 132 to 256): 8 at 3 was 0-15%
-//                             faster than 4 at 4, 2 at 4, 16 at 2, 2 or 4 at
-//                             5 at K = 144 ... 256.
 //   LDA_GROUP_LEAF            topics per lane of the leaf-group kernel (4 or
 //                             8: groups of K / 4 or K / 8 lanes, rounded up
 //                             to a power of two).
 #ifndef LDA_GROUP_LEAF
 #define LDA_GROUP_LEAF 4
 #endif
-//   LDA_GROUP_KEEP_MAX_G      largest group (lanes) of 4-topic leaves that
-//                             keeps its leaves' partial sums in LDS for the
-//                             final scan instead of reloading the chosen leaf
-//                             (0: none).  Groups of 8 (K <= 32): 9-16% faster
-//                             at 3-4M tokens (6.75 KiB per wavefront: 22
-//                             wavefronts per CU instead of 24); groups of 16:
-//                             4-12% slower (12.75 KiB: 12 instead of 20).
-#ifndef LDA_GROUP_KEEP_MAX_G
-#define LDA_GROUP_KEEP_MAX_G 8
-#endif
-#ifndef LDA_GROUP64_WINDOW
-#define LDA_GROUP64_WINDOW 8
-#endif
-#ifndef LDA_GROUP64_WAVES_PER_EU
-#define LDA_GROUP64_WAVES_PER_EU 3
-#endif
-//   LDA_LEAF8_MAX_K, LDA_LEAF8_ALIGNED_MAX_K
-//                             K above 256 drawn by groups of 64 lanes with
-//                             8-topic leaves, the whole row in one tile (K
-//                             divisible by 4): up to LDA_LEAF8_MAX_K (at most
-//                             512; 0: none), except multiples of 32 above
-//                             LDA_LEAF8_ALIGNED_MAX_K; the eighths kernel
-//                             draws the rest.  Measured on the 16.8M-token
-//                             corpus against the eighths kernel: 17-21%
-//                             faster at K = 260 ... 320, 7% at 384, 1-4% at
-//                             392 ... 508 (416 included); 2-3% slower at 448,
-//                             480 and 512 (rows of whole 128-byte lines).
-//   LDA_LEAF8_WINDOW, LDA_LEAF8_WAVES_PER_EU  their tokens in flight per
-//                             wavefront and wavefronts per SIMD: 4 at 3
-//                             (154-160 VGPRs) was 3-6% faster than 8 at 2 at
-//                             K = 260 ... 384 and within 0.5% above; 2 at 4
-//                             spills.
+//   LDA_LEAF8_MAX_K           largest K above 256 drawn by groups of 64 lanes
+//                             with 8-topic leaves, the whole row in one tile
+//                             (at most 512; 0: none); the eighths kernel draws
+//                             the rest (see leaf8_for).
+//   LDA_LEAF8_WINDOW, LDA_LEAF8_WAVES_PER_EU  tokens in flight per wavefront
+//                             and wavefronts per SIMD of 8-topic leaves: 4 at
+//                             3 (158 VGPRs) took 282-470 us at K = 260 ... 512
+//                             on 4M tokens, 2 at 4 305-467, 8 at 3 340-545.
 #ifndef LDA_LEAF8_MAX_K
-#define LDA_LEAF8_MAX_K 508
-#endif
-#ifndef LDA_LEAF8_ALIGNED_MAX_K
-#define LDA_LEAF8_ALIGNED_MAX_K 416
+#define LDA_LEAF8_MAX_K 512
 #endif
 #ifndef LDA_LEAF8_WINDOW
 #define LDA_LEAF8_WINDOW 4

@@ -1,0 +1,49 @@
+"""The leaf-group kernel at the edges of its rows: K around every group width
+(16, 32, 64, 128, 256, 512), K of every remainder mod 4 (the first quad of a
+row then holds 1 to 3 topics), documents of every mode (one per group, a few
+runs, any), the window's tail, and both table builds."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from paper_1505_03851_amd.inputs import make_random
+from parity import compare, run_kernel, to_device
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("K", [4, 5, 15, 16, 17, 30, 33, 63, 65, 67, 126, 129, 131, 250, 255, 257,
+                               259, 385, 447, 509, 511, 512])
+def test_rows_of_every_width(K):
+    # documents of 128 tokens (with 32-lane groups: sums kept in registers),
+    # of about 20 (runs), one token each in turn (any)
+    for N, M, order in ((64 * 33 + 1, 16, "sequential"), (64 * 33 + 63, 100, "ragged"),
+                        (64 * 9 + 17, 40, "shuffled")):
+        # (weights away from fp32's subnormal range, where products vanish)
+        c = make_random(N, M, 300, K, seed=K, alpha=0.5, beta=0.5, doc_order=order)
+        dev = to_device(c)
+        z = {k: run_kernel(k, dev) for k in ("butterfly", "variant-wide", "variant-leaf8")}
+        for name, got in z.items():
+            rep = compare(c, got)
+            print(f"[parity] {c.name} {name}: {rep}", flush=True)
+            assert rep.hard == 0, (name, rep.first_hard)
+        assert np.array_equal(z["butterfly"], z["variant-wide"])
+
+
+@pytest.mark.parametrize("K", [5, 18, 35, 66, 131, 259])
+def test_tiny_uniforms_behind_empty_components(K):
+    """Stops of 0 and of a few ulps of S, and the largest u, with every second
+    topic weightless: no draw ends in an empty component of the first quad or
+    at a topic the rounding band does not admit."""
+    N = 640
+    c = make_random(N, 8, 60, K, seed=K, alpha=0.5, beta=0.5)
+    theta = c.theta.copy()
+    theta[1::2, ::2] = 0.0
+    theta[0] = 0.0
+    u = (np.arange(N) % 5).astype(np.float32) * np.float32(2.0 ** -24)
+    u[4::5] = np.float32(1.0 - 2.0 ** -24)
+    c = dataclasses.replace(c, theta=theta, u=u)
+    for kernel in ("butterfly", "variant-wide"):
+        rep = compare(c, run_kernel(kernel, to_device(c)))
+        assert rep.hard == 0, (kernel, rep.first_hard)
