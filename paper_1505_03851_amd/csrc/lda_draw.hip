@@ -49,6 +49,7 @@
 #include "doc_lanes.hpp"
 #include "counts.hpp"
 #include "word_index.hpp"
+#include "count_cells.hpp"
 
 namespace lda {
 namespace {
@@ -635,6 +636,53 @@ unsigned doc_grid(int32_t M) {
 }  // namespace
 }  // namespace lda
 
+namespace lda {
+namespace {
+
+void launch_clear(int32_t *table, int64_t cells, hipStream_t s) {
+  const int64_t blocks = (cells / 4 + 255) / 256;
+  count_clear<<<(unsigned)(blocks < 4096 ? (blocks > 0 ? blocks : 1) : 4096), 256, 0, s>>>(table,
+                                                                                       cells);
+}
+
+template <int PER, int BITS>
+bool launch_cells(const int32_t *doc_id, const int32_t *word_id, const int32_t *z, int64_t N,
+                  int32_t M, int32_t V, int32_t K, int32_t *ndk, int32_t *nwk, hipStream_t s) {
+  using S = CellSplit<PER, BITS>;
+  if (S::bytes(N) > 4 * (int64_t)M * K) return false;
+  const int64_t chunks = S::chunks(N);
+  uint32_t *runs = reinterpret_cast<uint32_t *>(ndk);
+  uint16_t *offs = reinterpret_cast<uint16_t *>(ndk + N);
+  count_split_kernel<PER, BITS><<<(unsigned)chunks, kSplitThreads, 0, s>>>(
+      doc_id, word_id, z, N, M, V, K, runs, offs, nwk, (int64_t)V * K);
+  count_cells_kernel<PER, BITS><<<S::kBuckets, kCellThreads, 0, s>>>(runs, offs, (uint32_t)chunks,
+                                                                     nwk);
+  return true;
+}
+
+// The word table by partition of its cells (count_cells.hpp), with ndk as
+// scratch; false (nothing launched) where ndk cannot hold it (about as many
+// tokens as cells of ndk, or more) or N is too small to pay.  doc_id null:
+// offsets form.  Measured on MI355X, whole calls, before -> now: with document
+// ids 72 -> 51 us on 1M tokens at K = 256 and 1,086 -> 610 on 16.8M at K =
+// 1024; with offsets 145 -> 54 on the paper-shaped corpus at K = 112, 347 ->
+// 100 on 8M at K = 200; over the word index 473 -> 352 on 16.8M at K = 1024, 34.5
+// -> 33.9 on 1M at K = 256.  At 500,000 tokens 41 -> 39, 34 -> 29 and 29.5 ->
+// 28.9; at 200,000 and K = 1000 35 -> 42: the line is drawn between.
+bool count_cells(const int32_t *doc_id, const int32_t *word_id, const int32_t *z, int64_t N,
+                 int32_t M, int32_t V, int32_t K, int32_t *ndk, int32_t *nwk, hipStream_t s) {
+  if (N < LDA_COUNT_SPLIT_MIN_N) return false;
+  // Chunks of 4,096 tokens fill the chip (1M tokens: 256 workgroups); from 8M
+  // on, of 8,192 tokens in 512 buckets (16.8M at K = 1024: 352 us against 460;
+  // 3M at K = 112: 51.5 against 53.7, 1M at K = 256: 57 against 51).
+  if (N < 8000000)
+    return launch_cells<8, 8>(doc_id, word_id, z, N, M, V, K, ndk, nwk, s);
+  return launch_cells<16, 9>(doc_id, word_id, z, N, M, V, K, ndk, nwk, s);
+}
+
+}  // namespace
+}  // namespace lda
+
 extern "C" int lda_count_topics(const int32_t *doc_id, const int32_t *word_id, const int32_t *z,
                                 int64_t N, int32_t M, int32_t V, int32_t K, int32_t *ndk,
                                 int32_t *nwk, void *stream) {
@@ -650,18 +698,18 @@ extern "C" int lda_count_topics(const int32_t *doc_id, const int32_t *word_id, c
   for (const void *p : ptrs)
     if (reinterpret_cast<uintptr_t>(p) & 3u) return LDA_ERR_ALIGN;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int64_t cells[2] = {(int64_t)M * K, (int64_t)V * K};
-  int32_t *tables[2] = {ndk, nwk};
-  for (int t = 0; t < 2; ++t) {
-    const int64_t blocks = (cells[t] / 4 + 255) / 256;
-    count_clear<<<(unsigned)(blocks < 4096 ? (blocks > 0 ? blocks : 1) : 4096), 256, 0, s>>>(
-        tables[t], cells[t]);
+  const int64_t chunks = (N + kCountChunk - 1) / kCountChunk;
+  if (count_cells(doc_id, word_id, z, N, M, V, K, ndk, nwk, s)) {
+    launch_clear(ndk, (int64_t)M * K, s);
+    count_doc_ids_kernel<<<(unsigned)((N + kDocIdChunk - 1) / kDocIdChunk), kCountThreads, 0, s>>>(
+        doc_id, word_id, z, N, M, V, K, ndk);
+    return finish_launch();
   }
-  if (N > 0) {
-    const int64_t chunks = (N + kCountChunk - 1) / kCountChunk;
+  launch_clear(ndk, (int64_t)M * K, s);
+  launch_clear(nwk, (int64_t)V * K, s);
+  if (N > 0)
     count_kernel<<<(unsigned)chunks, kCountThreads, 0, s>>>(doc_id, word_id, z, N, M, V, K, ndk,
                                                             nwk);
-  }
   return finish_launch();
 }
 
@@ -680,14 +728,12 @@ extern "C" int lda_count_topics_docs(const int64_t *doc_offsets, const int32_t *
     if (reinterpret_cast<uintptr_t>(p) & 3u) return LDA_ERR_ALIGN;
   if (reinterpret_cast<uintptr_t>(doc_offsets) & 7u) return LDA_ERR_ALIGN;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int64_t cells = (int64_t)V * K;
-  const int64_t blocks = (cells / 4 + 255) / 256;
-  count_clear<<<(unsigned)(blocks < 4096 ? (blocks > 0 ? blocks : 1) : 4096), 256, 0, s>>>(
-      nwk, cells);
+  const bool counted = count_cells(nullptr, word_id, z, N, M, V, K, ndk, nwk, s);
+  if (!counted) launch_clear(nwk, (int64_t)V * K, s);
   const size_t lds = (size_t)kDocWaves * (size_t)K * sizeof(uint32_t);
   count_docs_kernel<<<doc_grid(M), kDocWaves * 64, lds, s>>>(doc_offsets, word_id, z, N, M, V,
                                                               K, ndk);
-  if (N > 0) {
+  if (N > 0 && !counted) {
     const int64_t chunks = (N + kCountChunk - 1) / kCountChunk;
     count_words_kernel<<<(unsigned)chunks, kCountThreads, 0, s>>>(word_id, z, N, V, K, nwk);
   }
@@ -797,14 +843,12 @@ extern "C" int lda_count_topics_indexed(const int64_t *doc_offsets, const int32_
   const WordIndexLayout L = word_index_layout(N, V);
   const char *b = static_cast<const char *>(index);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int64_t cells = (int64_t)V * K;
-  const int64_t blocks = (cells / 4 + 255) / 256;
-  count_clear<<<(unsigned)(blocks < 4096 ? (blocks > 0 ? blocks : 1) : 4096), 256, 0, s>>>(
-      nwk, cells);
+  const bool counted = count_cells(nullptr, word_id, z, N, M, V, K, ndk, nwk, s);
+  if (!counted) launch_clear(nwk, (int64_t)V * K, s);
   const size_t lds = (size_t)kDocWaves * (size_t)K * sizeof(uint32_t);
   count_docs_kernel<<<doc_grid(M), kDocWaves * 64, lds, s>>>(doc_offsets, word_id, z, N, M, V,
                                                               K, ndk);
-  if (N > 0) {
+  if (N > 0 && !counted) {
     const int run = index_run(N);
     const int64_t per = (int64_t)run * kCountChunk;
     count_words_indexed<<<(unsigned)((N + per - 1) / per), kCountThreads, 0, s>>>(

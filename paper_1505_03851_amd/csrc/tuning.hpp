@@ -111,3 +111,9 @@
 #ifndef LDA_ROUTED_FEW_THETA
 #define LDA_ROUTED_FEW_THETA 4
 #endif
+//   LDA_COUNT_SPLIT_MIN_N     smallest number of tokens whose word counts are
+//                             taken by partition of the cells (count_cells in
+//                             lda_draw.hip).
+#ifndef LDA_COUNT_SPLIT_MIN_N
+#define LDA_COUNT_SPLIT_MIN_N 524288
+#endif
