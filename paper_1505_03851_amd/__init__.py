@@ -25,5 +25,6 @@ __all__ = list(_BINDING)
 def __getattr__(name):
     if name in _BINDING:
         from . import _lib
-        return getattr(_lib, name)
+        globals()[name] = value = getattr(_lib, name)  # found at once from now on
+        return value
     raise AttributeError(name)

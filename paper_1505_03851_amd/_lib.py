@@ -175,6 +175,53 @@ def _shapes(theta, phi, doc_id, word_id, u=None):
     return N, M, V, K
 
 
+# The checks above cost several microseconds a call, as long as a small draw
+# takes on the GPU.  A call whose arguments are all as they should be -- plain
+# dense tensors of the right types on the current device -- is recognised by the
+# fewest attribute reads and goes straight to the library; any other call takes
+# the full checks, which raise the error or handle it (another device, say).
+_F32, _I32, _I64 = torch.float32, torch.int32, torch.int64
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
+def _fast_device(t):
+    """The device index of tensor ``t`` if it is the current GPU, else None."""
+    if type(t) is not torch.Tensor or _raw_stream is None or _current_device is None:
+        return None
+    dev = t.get_device()
+    return dev if dev >= 0 and dev == _current_device() else None
+
+
+def _fast_tables(theta, phi, dev):
+    """(M, V, K) if theta and phi are dense tables of one K on ``dev`` (theta's
+    device)."""
+    if (type(phi) is torch.Tensor and theta.dtype is _F32 and phi.dtype is _F32
+            and theta.dim() == 2 and phi.dim() == 2 and phi.get_device() == dev
+            and theta.is_contiguous() and phi.is_contiguous()):
+        M, K = theta.shape
+        V, K2 = phi.shape
+        if K == K2:
+            return M, V, K
+    return None
+
+
+def _vec(t, dtype, dev, N) -> bool:
+    """Whether ``t`` is a dense vector of N entries on ``dev``."""
+    return (type(t) is torch.Tensor and t.dtype is dtype and t.dim() == 1 and t.numel() == N
+            and t.get_device() == dev and t.is_contiguous())
+
+
+def _call(fn_name, *args):
+    st = getattr(_lib or load(), fn_name)(*args)
+    if st != 0:
+        _check(st)
+
+
+def _handle(stream, dev) -> int:
+    return _raw_stream(dev) if stream is None else int(stream.cuda_stream)
+
+
 def _validate_ids(doc_id, word_id, M, V) -> None:
     if doc_id.numel():
         if int(doc_id.min()) < 0 or int(doc_id.max()) >= M:
@@ -184,6 +231,19 @@ def _validate_ids(doc_id, word_id, M, V) -> None:
 
 
 def _draw(fn_name, theta, phi, doc_id, word_id, u, out, stream, validate, extra=()):
+    dev = None if validate else _fast_device(theta)
+    if dev is not None:
+        shape = _fast_tables(theta, phi, dev)
+        if shape is not None and type(doc_id) is torch.Tensor:
+            N = doc_id.numel()
+            if (_vec(doc_id, _I32, dev, N) and _vec(word_id, _I32, dev, N)
+                    and _vec(u, _F32, dev, N) and (out is None or _vec(out, _I32, dev, N))):
+                if out is None:
+                    out = torch.empty(N, dtype=_I32, device=theta.device)
+                _call(fn_name, theta.data_ptr(), phi.data_ptr(), doc_id.data_ptr(),
+                      word_id.data_ptr(), u.data_ptr(), out.data_ptr(), N, *shape, *extra,
+                      _handle(stream, dev))
+                return out
     N, M, V, K = _shapes(theta, phi, doc_id, word_id, u)
     if validate:
         _validate_ids(doc_id, word_id, M, V)
@@ -243,6 +303,20 @@ def draw_philox(theta, phi, doc_id, word_id, seed: int, sweep: int = 0, out=None
     """z[N] (int32) by the butterfly kernel with the uniforms generated in the
     kernel (Philox4x32-10 of token index, sweep and seed; see
     ``philox_uniforms``)."""
+    dev = None if validate else _fast_device(theta)
+    if dev is not None:
+        shape = _fast_tables(theta, phi, dev)
+        if shape is not None and type(doc_id) is torch.Tensor:
+            N = doc_id.numel()
+            if (_vec(doc_id, _I32, dev, N) and _vec(word_id, _I32, dev, N)
+                    and (out is None or _vec(out, _I32, dev, N))):
+                if out is None:
+                    out = torch.empty(N, dtype=_I32, device=theta.device)
+                _call("lda_draw_butterfly_philox", theta.data_ptr(), phi.data_ptr(),
+                      doc_id.data_ptr(), word_id.data_ptr(), out.data_ptr(), N, *shape,
+                      int(seed) & (2 ** 64 - 1), int(sweep) & (2 ** 32 - 1),
+                      _handle(stream, dev))
+                return out
     N, M, V, K = _shapes(theta, phi, doc_id, word_id)
     if validate:
         _validate_ids(doc_id, word_id, M, V)
@@ -301,6 +375,19 @@ def draw_doc_lanes(theta, phi, doc_offsets, word_id, u, theta_cache: bool = Fals
 
 def _draw_offsets(fn_name, theta, phi, doc_offsets, word_id, u, out, stream, validate,
                   extra=()):
+    dev = None if validate else _fast_device(theta)
+    if dev is not None:
+        shape = _fast_tables(theta, phi, dev)
+        if shape is not None and type(word_id) is torch.Tensor:
+            N = word_id.numel()
+            if (_vec(doc_offsets, _I64, dev, shape[0] + 1) and _vec(word_id, _I32, dev, N)
+                    and _vec(u, _F32, dev, N) and (out is None or _vec(out, _I32, dev, N))):
+                if out is None:
+                    out = torch.empty(N, dtype=_I32, device=theta.device)
+                _call(fn_name, theta.data_ptr(), phi.data_ptr(), doc_offsets.data_ptr(),
+                      word_id.data_ptr(), u.data_ptr(), out.data_ptr(), N, *shape, *extra,
+                      _handle(stream, dev))
+                return out
     _require(theta, "theta", torch.float32, 2)
     _require(phi, "phi", torch.float32, 2)
     _require(doc_offsets, "doc_offsets", torch.int64, 1)
