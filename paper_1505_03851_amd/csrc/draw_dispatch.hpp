@@ -106,6 +106,17 @@ bool groups_for(int64_t N, int32_t K) {
 // 128 tokens per document about half the groups' pairs lie in one document.
 bool long_docs(int64_t N, int32_t M) { return N >= 128 * (int64_t)M; }
 
+// Where the kernel looks for scattered documents (spread_draw), and log2 of the
+// tokens of a wavefront's share: documents as ids, theta past an XCD's 4 MiB of
+// L2, and tokens enough that every eighth wavefront's windows fill the chip.
+// Measured on MI355X: with theta of 4 MiB at 1M tokens 63 -> 75 us, of 8 MiB 85
+// -> 83, of 16 MiB 189 -> 139.  Shares of 2^11 (four windows of 64 on average):
+// 142 us at 2M tokens, K = 128; of 2^10 235 (a last window that is mostly
+// empty), of 2^12 153 (too few wavefronts; at 1M tokens 207 against 139).
+int spread_for(const DocSource &d, int64_t N, int32_t M, int32_t K) {
+  return d.ids && N >= (1 << 20) && (int64_t)M * K * 4 >= (6 << 20) ? 11 : 0;
+}
+
 template <int G, int H, int C, int WPEU, bool KEEP>
 void launch_groups_as(const float *theta, const float *phi, DocSource d, const int32_t *wd,
                       UniformSource u, int32_t *z, int64_t N, int32_t M, int32_t V, int32_t K,
@@ -113,12 +124,13 @@ void launch_groups_as(const float *theta, const float *phi, DocSource d, const i
   const uint32_t tb = table_extent(M, K);
   const uint32_t pb = table_extent(V, K);
   const size_t lds = (size_t)kWavesPerBlock * group_lds_bytes<G, H>();
+  const int spread = kSpread<G, H> ? spread_for(d, N, M, K) : 0;
   if (K == kLeaf * H * G)
     leaf_group_kernel<G, H, C, WPEU, KEEP, false><<<wave_grid(N), kBlockThreads, lds, s>>>(
-        theta, phi, d, wd, u, z, N, K, tb, pb);
+        theta, phi, d, wd, u, z, N, K, tb, pb, spread);
   else
     leaf_group_kernel<G, H, C, WPEU, KEEP, true><<<wave_grid(N), kBlockThreads, lds, s>>>(
-        theta, phi, d, wd, u, z, N, K, tb, pb);
+        theta, phi, d, wd, u, z, N, K, tb, pb, spread);
 }
 
 // Launch shapes by group and leaf (tuning.hpp).

@@ -107,11 +107,19 @@ constexpr int kGroupLast =
 // Groups of 8 lanes transpose their leaf sums in registers.
 template <int G>
 constexpr int kSumFloats = G == 8 ? 0 : GroupTile<G>::kFloats;
+// Tokens whose documents are scattered (see spread_draw): groups that take
+// them by document class, the classes (XCDs), and the doc ids read at a time.
+template <int G, int H>
+constexpr bool kSpread = G >= 32 && H == 1;
+constexpr int kSpreadClasses = 8;
+constexpr int kSpreadBatch = 4;
+constexpr int kSpreadRing = (kSpreadBatch + 1) * kWave;  // listed tokens, 16 bits each
 template <int G, int H>
 constexpr int group_lds_bytes() {
   constexpr bool lds = kGroupLast<G, H, false, kGroupOne> == kKeepInLds;
   return (kSumFloats<G> + (lds ? kWave * (G + 1) * 3 : 0)) * (int)sizeof(float) +
-         (lds ? 0 : kMaxGroupRuns<G> * H * kWave * (int)sizeof(f4));
+         (lds ? 0 : kMaxGroupRuns<G> * H * kWave * (int)sizeof(f4)) +
+         (kSpread<G, H> ? kSpreadRing * (int)sizeof(uint16_t) : 0);
 }
 
 using f3 = float __attribute__((ext_vector_type(3)));
@@ -222,7 +230,8 @@ struct GroupTokens {
   float u;
   int run;
   bool store;
-  int64_t n;
+  int at;      // the token's place after the window's first (its lane, unless
+               // the tokens are listed)
 };
 
 // A token whose leaf is known and whose leaf's factors are on their way.
@@ -242,7 +251,7 @@ struct GroupFound {
 
 // Search of one tile: the P lanes of each token agree on the lane, quad and
 // leaf that hold u * S.  `sums`: the tile's leaf sums in LDS.
-template <int G, int H, int MODE>
+template <int G, int H, int MODE, bool LISTED>
 __device__ __forceinline__ GroupFound<H> group_search(const GroupTokens &tok, const float *sums,
                                                       int tile, int c0, int32_t *z) {
   using S = GroupTile<G>;
@@ -253,7 +262,6 @@ __device__ __forceinline__ GroupFound<H> group_search(const GroupTokens &tok, co
   const int owner = g * G + tile * S::kLoads + j;  // lane that owns the token
   // the token's values, from the lane that owns it (this one with P = 1)
   GroupTokens my = tok;
-  int64_t n = tok.n;
   if constexpr (P > 1) {
     const int a = owner << 2;
     my.ph_lane = (uint32_t)__builtin_amdgcn_ds_bpermute(a, (int)tok.ph_lane);
@@ -263,7 +271,7 @@ __device__ __forceinline__ GroupFound<H> group_search(const GroupTokens &tok, co
     if constexpr (MODE == kGroupRuns) my.run = __builtin_amdgcn_ds_bpermute(a, tok.run);
     const uint64_t stores = __builtin_amdgcn_ballot_w64(tok.store);
     my.store = (stores >> owner) & 1;
-    n = tok.n - lane + owner;
+    my.at = LISTED ? __builtin_amdgcn_ds_bpermute(a, tok.at) : owner;
   }
   const float *row = sums + g * S::kGroup + j * S::kRow + S::leaf(p * S::kLeaves);
   float q[S::kQuads];
@@ -320,7 +328,7 @@ __device__ __forceinline__ GroupFound<H> group_search(const GroupTokens &tok, co
   f.leaf = leaf;
   f.first = c0 + kLeaf * H * leaf;
   f.slot = t;
-  f.z = z + n;
+  f.z = z + my.at;
   f.ph_row = my.ph_lane;
   f.th_row = my.th_lane;
   f.run = MODE == kGroupRuns ? my.run : 0;
@@ -363,7 +371,7 @@ __device__ __forceinline__ GroupFound<H> group8_search(const GroupTokens &tok, f
   f.slot = lane;
   f.who = true;
   f.mine = tok.store;
-  f.z = z + tok.n;
+  f.z = z + tok.at;
   f.ph_row = tok.ph_lane;
   f.th_row = tok.th_lane;
   f.run = tok.run;
@@ -466,7 +474,7 @@ __device__ __forceinline__ void group_finish_kept(const GroupFound<1> &f,
 // The tiles of a wavefront: leaf sums, search and topics of its 64 tokens.
 // voff[h]: byte offset of quad h of this lane's leaf in a row; real[h]: the
 // topics it holds, in its first components (0: front padding).
-template <int G, int H, int C, bool KEEP, int MODE, bool PAD>
+template <int G, int H, int C, bool KEEP, int MODE, bool PAD, bool LISTED = false>
 __device__ __forceinline__ void group_tiles(const Table &th_t, const Table &ph_t,
                                             const uint32_t (&voff)[H], const int (&real)[H],
                                             const GroupTokens &tok, int gbase, uint64_t gstarts,
@@ -639,7 +647,7 @@ __device__ __forceinline__ void group_tiles(const Table &th_t, const Table &ph_t
       if constexpr (G == 8)
         now = group8_search<H>(tok, a, c0, z);
       else
-        now = group_search<G, H, MODE>(tok, sums, k / S::kLoads, c0, z);
+        now = group_search<G, H, MODE, LISTED>(tok, sums, k / S::kLoads, c0, z);
       if constexpr (LAST == kKeepInRegs) {
         lds_order();
         group_finish_kept<G, PAD>(now, kept, sums, drop);
@@ -658,45 +666,157 @@ __device__ __forceinline__ void group_tiles(const Table &th_t, const Table &ph_t
   if constexpr (LAST == kReload) group_finish<H, PAD>(found, drop);
 }
 
+// What a lane's leaf needs of a row: padded index of the first leaf's first
+// topic, empty components of the first quad, and per quad of this lane's leaf
+// its byte offset and the topics it holds.
+template <int H>
+struct GroupLeaf {
+  int c0, drop;
+  uint32_t voff[H];
+  int real[H];
+};
+template <int G, int H, bool PAD>
+__device__ __forceinline__ GroupLeaf<H> group_leaf(int K, int r) {
+  GroupLeaf<H> l;
+  l.drop = PAD ? (-K) & (kLeaf - 1) : 0;
+  l.c0 = K + l.drop - kLeaf * H * G;
+#pragma unroll
+  for (int h = 0; h < H; ++h) {
+    const int i = l.c0 + kLeaf * H * r + kLeaf * h;
+    l.real[h] = !PAD || i >= kLeaf ? kLeaf : (i < 0 ? 0 : kLeaf - l.drop);
+    l.voff[h] = (uint32_t)(!PAD ? i : (i >= kLeaf ? i - l.drop : 0)) * 4u;
+  }
+  return l;
+}
+
+// Tokens whose documents are scattered (shuffled tokens): theta rows, like phi
+// rows, then come from all over their table in every XCD, and misses past L2
+// bound the draw.  Eight workgroups, one per XCD (workgroup b runs on XCD b
+// mod 8), share a stretch of tokens instead: each wavefront reads the doc ids
+// of its share of the stretch, lists the tokens whose document's class is its
+// workgroup's, and draws them 64 at a time, so that an XCD's L2 holds one
+// eighth of theta.  Measured on MI355X, tokens shuffled: 2M tokens, V = 50,000,
+// theta of 8 MiB at K = 128 172 -> 142 us, of 12.5 MiB at K = 200 317 -> 233;
+// 1M tokens, 16 MiB at K = 256 189 -> 139; tokens in document order within 1%
+// (the check's doc ids are loaded with the wavefront's own).  `ids`, `word_id`,
+// `z`: from the share's first token on; `first`: its index, for `u`.
+template <int G, int H, int C, bool KEEP, bool PAD>
+__device__ __forceinline__ void spread_draw(const Table &th_t, const Table &ph_t,
+                                            const int32_t *ids, const int32_t *word_id,
+                                            const UniformSource &u, int64_t first, int tokens,
+                                            uint32_t cls, const GroupLeaf<H> &leaf, float *sums,
+                                            f4 *stage, uint16_t *ring, int32_t *z) {
+  const int lane = lane_id(), gbase = lane & ~(G - 1);
+  const uint64_t below = (1ull << lane) - 1ull;
+  constexpr int step = kSpreadBatch * kWave;
+  int32_t doc[kSpreadBatch];
+  const auto load = [&](int from) {
+#pragma unroll
+    for (int i = 0; i < kSpreadBatch; ++i) {
+      const int at = from + i * kWave + lane;
+      doc[i] = at < tokens ? ids[at] : 0;
+    }
+  };
+  load(0);
+  int have = 0;  // listed tokens not yet drawn
+  int from = 0;
+  while (true) {
+    while (have < kWave && from < tokens) {
+#pragma unroll
+      for (int i = 0; i < kSpreadBatch; ++i) {
+        const int at = from + i * kWave + lane;
+        const bool mine = at < tokens && ((uint32_t)doc[i] * 2654435761u) >> 29 == cls;
+        const uint64_t picks = __builtin_amdgcn_ballot_w64(mine);
+        if (mine) ring[have + __builtin_popcountll(picks & below)] = (uint16_t)at;
+        have += __builtin_popcountll(picks);
+      }
+      from += step;
+      if (from < tokens) load(from);  // (in flight during the next window)
+      lds_order();
+    }
+    if (have == 0) return;
+    const int take = have < kWave ? have : kWave;
+    have -= take;
+    GroupTokens tok;
+    tok.at = ring[have + (lane < take ? lane : take - 1)];
+    tok.store = lane < take;
+    tok.ph_lane = ph_t.row((uint32_t)word_id[tok.at]);
+    tok.th_lane = th_t.row((uint32_t)ids[tok.at]);
+    tok.u = u(first + tok.at);
+    tok.run = 0;
+    group_tiles<G, H, C, KEEP, kGroupAny, PAD, true>(th_t, ph_t, leaf.voff, leaf.real, tok, gbase,
+                                                     0, sums, stage, leaf.c0, leaf.drop, z);
+    lds_order();
+  }
+}
+
 // L = 4 H topics per lane: groups of G lanes cover 4 H G topics.
 template <int G, int H, int C, int WPEU, bool KEEP, bool PAD>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(WPEU)))
 void leaf_group_kernel(const float *__restrict__ theta, const float *__restrict__ phi,
                        DocSource docs, const int32_t *__restrict__ word_id,
                        UniformSource u, int32_t *__restrict__ z, int64_t N, int K,
-                       uint32_t theta_extent, uint32_t phi_extent) {
-  constexpr int L = kLeaf * H;
+                       uint32_t theta_extent, uint32_t phi_extent, int spread) {
   extern __shared__ __align__(16) float lds[];
   const int lane = lane_id();
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   float *sums = lds + wave * (group_lds_bytes<G, H>() / (int)sizeof(float));
   f4 *stage = reinterpret_cast<f4 *>(sums + kSumFloats<G>);
   const int64_t first = ((int64_t)blockIdx.x * kWavesPerBlock + wave) * kWave;
-  if (first >= N) return;  // whole wavefront past the end
+  const int r = lane & (G - 1), gbase = lane & ~(G - 1);
   // Window of 64 tokens as in butterfly_kernel (N >= 64 here).
   const int64_t t0 = first + kWave <= N ? first : N - kWave;
   GroupTokens tok;
-  tok.n = t0 + lane;
-  tok.store = tok.n >= first;
-  const int doc = docs.wave_doc(tok.n, t0, t0 + kWave - 1);
-  const int word = word_id[tok.n];
-  tok.u = u(tok.n);
+  const int64_t n = t0 + lane;
+  tok.at = lane;
+  tok.store = n >= first;
+  int doc = docs.ids ? docs.ids[n] : 0;
+  const int word = word_id[n];
+  tok.u = u(n);
+  // Windows of the modes that keep their sums in registers: for groups of 16
+  // all 16 tokens in one document (the sums take the loaded leaves' place),
+  // fewer where theta comes per token too.
+  constexpr bool K16 = G == 16 && H == 1 && KEEP;
+  constexpr int C1 = K16 ? G : C;
+  constexpr int CA = K16 ? (PAD ? 2 : 4) : (G == kWave && H == 1 ? C / 2 : C);
+  if constexpr (kSpread<G, H>) {
+    // spread: log2 of the tokens per wavefront's share of a stretch (0: never).
+    // A stretch whose first 64 tokens change document more than every other
+    // token is drawn by its first eight workgroups; the others are done.
+    const int64_t stretch = (int64_t)kWavesPerBlock << spread;
+    const int shift = spread ? spread - 6 : 0;  // log2 of a stretch's workgroups
+    const uint32_t index = blockIdx.x >> shift;
+    const int64_t s0 = index * stretch;
+    // (a last, incomplete stretch may have fewer than eight workgroups)
+    if (spread && s0 + stretch <= N) {
+      const int d = docs.ids[s0 + lane];
+      const int p = __builtin_amdgcn_update_dpp(d, d, 0x138, 0xF, 0xF, false);
+      if (__builtin_popcountll(__builtin_amdgcn_ballot_w64(d != p)) > kWave / 2) {
+        // (a stretch's eight by turns: an XCD's CUs get workgroups round robin)
+        const uint32_t part = blockIdx.x & ((1u << shift) - 1u);
+        const uint32_t turns = (1u << shift) / kSpreadClasses;
+        if (part / kSpreadClasses != (index & (turns - 1u))) return;
+        const int64_t lo = s0 + ((int64_t)wave << spread);
+        // (a window of 2 where 4 would not fit the registers)
+        constexpr int CS = G == 32 && !KEEP && !PAD ? 2 : CA;
+        spread_draw<G, H, CS, KEEP, PAD>(
+            make_table(theta, theta_extent, K), make_table(phi, phi_extent, K), docs.ids + lo,
+            word_id + lo, u, lo, 1 << spread, part % kSpreadClasses, group_leaf<G, H, PAD>(K, r),
+            sums, stage, reinterpret_cast<uint16_t *>(stage + kMaxGroupRuns<G> * H * kWave),
+            z + lo);
+        return;
+      }
+    }
+  }
+  if (first >= N) return;  // whole wavefront past the end
+  if (!docs.ids) doc = docs.wave_doc(n, t0, t0 + kWave - 1);
+  z += t0;
 
   const Table th_t = make_table(theta, theta_extent, K);
   const Table ph_t = make_table(phi, phi_extent, K);
   tok.ph_lane = ph_t.row((uint32_t)word);
   tok.th_lane = th_t.row((uint32_t)doc);
-  const int r = lane & (G - 1), gbase = lane & ~(G - 1);
-  const int drop = PAD ? (-K) & (kLeaf - 1) : 0;  // empty components of the first quad
-  const int c0 = K + drop - L * G;  // padded index of leaf 0's first topic
-  uint32_t voff[H];
-  int real[H];
-#pragma unroll
-  for (int h = 0; h < H; ++h) {
-    const int i = c0 + L * r + kLeaf * h;
-    real[h] = !PAD || i >= kLeaf ? kLeaf : (i < 0 ? 0 : kLeaf - drop);
-    voff[h] = (uint32_t)(!PAD ? i : (i >= kLeaf ? i - drop : 0)) * 4u;
-  }
+  const GroupLeaf<H> leaf = group_leaf<G, H, PAD>(K, r);
   // runs of documents inside each group: bit l of `starts` marks lane l's
   // token as the first of a run (not counting the group's first token)
   // (lane l's previous document by a DPP wavefront shift right by one lane:
@@ -712,21 +832,15 @@ void leaf_group_kernel(const float *__restrict__ theta, const float *__restrict_
   for (int g = 0; g < kWave / G; ++g)
     most = max(most, __builtin_popcountll((starts >> (g * G)) & gmask));
 
-  // Windows of the modes that keep their sums in registers: for groups of 16
-  // all 16 tokens in one document (the sums take the loaded leaves' place),
-  // fewer where theta comes per token too.
-  constexpr bool K16 = G == 16 && H == 1 && KEEP;
-  constexpr int C1 = K16 ? G : C;
-  constexpr int CA = K16 ? (PAD ? 2 : 4) : (G == kWave && H == 1 ? C / 2 : C);
   if (most == 0)
-    group_tiles<G, H, C1, KEEP, kGroupOne, PAD>(th_t, ph_t, voff, real, tok, gbase, 0, sums, stage, c0,
-                                         drop, z);
+    group_tiles<G, H, C1, KEEP, kGroupOne, PAD>(th_t, ph_t, leaf.voff, leaf.real, tok, gbase, 0,
+                                                sums, stage, leaf.c0, leaf.drop, z);
   else if (most < kMaxGroupRuns<G>)
-    group_tiles<G, H, C, KEEP, kGroupRuns, PAD>(th_t, ph_t, voff, real, tok, gbase, gstarts, sums,
-                                          stage, c0, drop, z);
+    group_tiles<G, H, C, KEEP, kGroupRuns, PAD>(th_t, ph_t, leaf.voff, leaf.real, tok, gbase,
+                                                gstarts, sums, stage, leaf.c0, leaf.drop, z);
   else
-    group_tiles<G, H, CA, KEEP, kGroupAny, PAD>(th_t, ph_t, voff, real, tok, gbase, 0, sums, stage, c0,
-                                         drop, z);
+    group_tiles<G, H, CA, KEEP, kGroupAny, PAD>(th_t, ph_t, leaf.voff, leaf.real, tok, gbase, 0,
+                                                sums, stage, leaf.c0, leaf.drop, z);
 }
 
 }  // namespace

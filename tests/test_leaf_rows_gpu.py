@@ -47,3 +47,32 @@ def test_tiny_uniforms_behind_empty_components(K):
     for kernel in ("butterfly", "variant-wide"):
         rep = compare(c, run_kernel(kernel, to_device(c)))
         assert rep.hard == 0, (kernel, rep.first_hard)
+
+
+@pytest.mark.parametrize("N,M,K", [((1 << 20), 16000, 128), ((1 << 20) + 4095, 24000, 101),
+                                   ((1 << 20) + 77, 7000, 256), ((1 << 20) + 4096, 9000, 190),
+                                   ((1 << 20) + 1, 30000, 66)])
+@pytest.mark.parametrize("order", ["shuffled", "partly"])
+def test_scattered_documents(N, M, K, order):
+    """Tokens in no document order, with theta past an XCD's L2: stretches of
+    the tokens are drawn by document class; "partly": stretches of either kind,
+    and a last one that is incomplete."""
+    c = make_random(N, M, 500, K, seed=K, alpha=0.5, beta=0.5,
+                    doc_order="shuffled" if order == "shuffled" else "sequential")
+    if order == "partly":
+        g = np.random.Generator(np.random.PCG64(K))
+        d = c.doc_id.copy()
+        for lo, hi in ((5000, 300000), (N - 9000, N)):
+            d[lo:hi] = g.permutation(d[lo:hi])
+        c = dataclasses.replace(c, doc_id=d)
+    dev = to_device(c)
+    z = {k: run_kernel(k, dev) for k in ("butterfly", "variant-wide")}
+    rep = compare(c, z["butterfly"])
+    print(f"[parity] {c.name} {order}: {rep}", flush=True)
+    assert rep.hard == 0, rep.first_hard
+    assert np.array_equal(z["butterfly"], z["variant-wide"])
+    import torch
+    import paper_1505_03851_amd as lda
+    a = (dev["theta"], dev["phi"], dev["doc_id"], dev["word_id"])
+    zp = lda.draw_philox(*a, 7, 3)
+    assert torch.equal(zp, lda.draw_butterfly(*a, lda.philox_uniforms(N, 7, 3)))
