@@ -775,14 +775,14 @@ PROFILE_TARGETS = {
                                      "--workload", HEADLINE, "--steps", "3", "--warmup", "1"]),
     "naive_K1024": ("naive_kernel", ["--only", "naive", "--workload", HEADLINE,
                                      "--steps", "2", "--warmup", "0"]),
-    "count_K1024": ("count_kernel", ["--only", "count", "--workload", HEADLINE,
+    "count_K1024": ("count_doc_ids_kernel", ["--only", "count", "--workload", HEADLINE,
                                      "--steps", "3", "--warmup", "1"]),
     "cdocs_K1024": ("count_docs_kernel", ["--only", "count-docs", "--workload", HEADLINE,
                                           "--steps", "3", "--warmup", "1"]),
-    "cwords_K1024": ("count_words_kernel", ["--only", "count-docs", "--workload", HEADLINE,
+    "csplit_K1024": ("count_split_kernel", ["--only", "count-docs", "--workload", HEADLINE,
                                             "--steps", "3", "--warmup", "1"]),
-    "cindexed_K1024": ("count_words_indexed", ["--only", "count-indexed", "--workload", HEADLINE,
-                                               "--steps", "3", "--warmup", "1"]),
+    "ccells_K1024": ("count_cells_kernel", ["--only", "count-docs", "--workload", HEADLINE,
+                                            "--steps", "3", "--warmup", "1"]),
     "draw_K256": ("leaf_group_kernel", ["--only", "butterfly", "--workload", SECOND,
                                         "--steps", "3", "--warmup", "1"]),
     "floor_K256": ("floor_kernel", ["--only", "floor", "--floor-config", "16,2,0",

@@ -16,15 +16,15 @@
 //                     the leaf kernel drawing them (lda_draw_routed_philox:
 //                     with in-kernel uniforms).
 // lda_count_topics    the per-document and per-word topic counts of a set of
-//                     draws (counts.hpp); lda_word_index_build and
+//                     draws (counts.hpp, large calls count_cells.hpp); lda_word_index_build and
 //                     lda_count_topics_indexed: the same counts with the tokens
 //                     grouped by word once per corpus (word_index.hpp).
 //
 // Device code: butterfly.hpp (lane exchanges, the butterfly, buffer loads),
 // philox.hpp, sources.hpp (document and uniform sources), tile.hpp (the
 // wavefront's tile loads and the in-block search), naive.hpp, one_topic.hpp
-// (one topic per lane), leaf_group.hpp (K up to 256), leaf_eighths.hpp (K
-// from 260 to 2048), route.hpp and routed_draw.hpp (routing to the XCDs),
+// (one topic per lane), leaf_group.hpp (K from 4 to 512), leaf_eighths.hpp
+// (K from 516 to 2048), route.hpp and routed_draw.hpp (routing to the XCDs),
 // transposed.hpp, table.hpp and doc_lanes.hpp (comparisons and the table
 // dump); tuning.hpp holds the build-time tuning.
 #include <hip/hip_runtime.h>
