@@ -240,8 +240,11 @@ __host__ __device__ constexpr uint32_t table_extent(int64_t rows, int32_t K) {
 }
 
 #if LDA_WIDE_TABLES
-// 16-byte loads at 4-byte alignment (a table's base need only be 4-byte aligned)
-using f4u = float __attribute__((ext_vector_type(4), aligned(4)));
+// 16-byte loads at 4-byte alignment: a table's base need only be 4-byte aligned,
+// nor does a row of K not divisible by 4 start at a multiple of 16 bytes.  (A
+// typedef: an alias declaration does not take the alignment.)
+typedef float f4u __attribute__((ext_vector_type(4), aligned(4)));
+static_assert(alignof(f4u) == 4, "f4u loads at any topic");
 
 struct Table {
   const float *base;

@@ -452,6 +452,7 @@ __device__ __forceinline__ void group_finish_kept(const GroupFound<1> &f,
                                                   const f3 (&kept)[GroupTile<G>::kLoads],
                                                   float *sums, int drop) {
   using S = GroupTile<G>;
+  static_assert(kWave + 4 * S::kTokens <= kSumFloats<G>, "leaves and slots take the sums' place");
   const int lane = lane_id(), r = lane & (G - 1), g = lane / G;
   int *leaves = reinterpret_cast<int *>(sums);
   f3 *slots = reinterpret_cast<f3 *>(sums + kWave);  // (16 bytes each)

@@ -1,0 +1,143 @@
+"""The leaf-group kernel's index arithmetic on the CPU: the kernel's own source
+built for the host (tests/leaf_host), a wavefront's lanes run in turn, under the
+address sanitizer.  Every global array has its exact size, of LDS only the
+running wavefront's region is accessible and a table load must stay inside its
+row, so an access out of range in any launch shape ends the run; the topics are
+compared with the oracle's.  Both table builds, every launch shape."""
+import dataclasses
+import os
+import shutil
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_1505_03851_amd.inputs import doc_offsets, make_random
+from parity import compare
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+CLANG = shutil.which("clang++", path="/opt/rocm/llvm/bin" + os.pathsep + os.environ["PATH"])
+
+
+@pytest.fixture(scope="module")
+def programs(tmp_path_factory):
+    if CLANG is None:
+        pytest.skip("no clang++")
+    out = tmp_path_factory.mktemp("leaf_host")
+    procs = {}
+    for wide in (0, 1):
+        exe = str(out / f"leaf_host{wide}")
+        procs[exe] = subprocess.Popen(
+            [CLANG, "-x", "c++", "-std=c++17", "-O1", "-g1", "-w", "-mllvm", "-unroll-threshold=0",
+             "-Xarch_host", "-fsanitize=address", f"-DLDA_WIDE_TABLES={wide}",
+             "-I", os.path.join(HERE, "leaf_host"),
+             "-I", os.path.join(ROOT, "paper_1505_03851_amd", "csrc"),
+             os.path.join(HERE, "leaf_host", "leaf_host.cpp"), "-o", exe])
+    assert all(p.wait() == 0 for p in procs.values())
+    return list(procs)
+
+
+def shape_of(N, M, K):
+    """(G, H, C, KEEP) of the dispatch."""
+    if K > 256:
+        return 64, 2, 4, 0
+    if K > 128:
+        return 64, 1, 8, 0
+    if K > 64:
+        return (32, 1, 8, 1) if N >= 128 * M else (32, 1, 4, 0)
+    if K > 32:
+        return 16, 1, 8, 1
+    return (8, 1, 8, 0) if K > 16 else (4, 1, 4, 0)
+
+
+def draw(program, c, shape, tmp, form="ids", offsets=None, spread=0, first=0, step=1):
+    src, dst = str(tmp / "in"), str(tmp / "out")
+    docs = c.doc_id
+    if form == "docs":
+        docs = doc_offsets(c.doc_id, c.M) if offsets is None else offsets
+    with open(src, "wb") as f:
+        f.write(np.array([c.N, c.M, c.V, c.K, int(form == "docs")], np.int64).tobytes())
+        for a in (c.theta, c.phi, docs, c.word_id, c.u):
+            f.write(np.ascontiguousarray(a).tobytes())
+    run = subprocess.run([program, src, dst, *map(str, (*shape, spread, first, step))],
+                         stderr=subprocess.PIPE, text=True,
+                         env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
+    assert run.returncode == 0, run.stderr[:3000]
+    return np.fromfile(dst, np.int32)
+
+
+KS = [4, 15, 16, 17, 32, 33, 50, 64, 65, 101, 112, 128, 129, 131, 208, 255, 256, 257, 448, 511, 512]
+
+
+@pytest.mark.parametrize("K", KS)
+def test_every_shape_in_bounds(K, programs, tmp_path):
+    for N, M, order in ((64 * 5 + 1, 2, "sequential"), (64 * 5 + 63, 12, "ragged"),
+                        (64 * 2, 60, "ragged"), (64 * 3 + 17, 40, "shuffled"), (64, 1, "single")):
+        c = make_random(N, M, 37, K, seed=K, alpha=0.5, beta=0.5, doc_order=order)
+        shapes = {shape_of(N, M, K)}
+        if 64 < K <= 128:
+            shapes = {(32, 1, 8, 1), (32, 1, 4, 0)}
+        for program in programs:
+            for shape in shapes:
+                for form in ("ids",) if order == "shuffled" else ("ids", "docs"):
+                    z = draw(program, c, shape, tmp_path, form)
+                    rep = compare(c, z)
+                    assert rep.hard == 0, (shape, form, order, rep.first_hard)
+
+
+@pytest.mark.parametrize("K", [20, 28, 32, 52, 64, 112, 128, 250, 256])
+def test_eight_topic_leaves_in_bounds(K, programs, tmp_path):
+    G = 4 if K <= 32 else 8 if K <= 64 else 16 if K <= 128 else 32
+    for N, M, order in ((64 * 3 + 5, 8, "ragged"), (64 * 2 + 17, 40, "shuffled")):
+        c = make_random(N, M, 37, K, seed=K, alpha=0.5, beta=0.5, doc_order=order)
+        rep = compare(c, draw(programs[0], c, (G, 2, 4, 0), tmp_path))
+        assert rep.hard == 0, rep.first_hard
+
+
+@pytest.mark.parametrize("K,M", [(112, 40), (66, 900), (128, 40), (131, 300), (256, 300)])
+def test_scattered_documents_in_bounds(K, M, programs, tmp_path):
+    """Stretches drawn by document class: two whole ones, an incomplete one."""
+    N = 2 * 8192 + 700
+    c = make_random(N, M, 200, K, seed=K, alpha=0.5, beta=0.5, doc_order="shuffled")
+    z = draw(programs[0], c, shape_of(N, M, K), tmp_path, spread=11)
+    rep = compare(c, z)
+    assert rep.hard == 0, rep.first_hard
+
+
+@pytest.mark.parametrize("K", [48, 112, 208, 300])
+def test_a_large_ragged_corpus_in_bounds(K, programs, tmp_path):
+    """Documents as offsets over six million tokens of lognormal lengths, empty
+    documents among them: wavefronts of the whole range."""
+    N, M = 6_000_001, 87_112
+    g = np.random.Generator(np.random.PCG64(K))
+    x = g.lognormal(0.0, 0.8, M) * (g.random(M) > 0.1)
+    x[-3:] = 0
+    off = np.concatenate([[0], np.rint(np.cumsum(x) * (N / x.sum()))]).astype(np.int64)
+    off[-4:] = N
+    ids = np.repeat(np.arange(M, dtype=np.int32), np.diff(off))
+    c = make_random(64, 5, 97, K, seed=K, alpha=0.5, beta=0.5)
+    c = dataclasses.replace(c, theta=np.tile(c.theta, (M // 5 + 1, 1))[:M], doc_id=ids,
+                            word_id=g.integers(0, 97, N, dtype=np.int32),
+                            u=g.random(N, dtype=np.float32))
+    z = draw(programs[0], c, shape_of(N, M, K), tmp_path, "docs", off, first=3, step=2503)
+    at = np.flatnonzero(z >= 0)
+    assert at.size >= 18 * 128 and at[-1] == N - 1
+    part = dataclasses.replace(c, doc_id=ids[at], word_id=c.word_id[at], u=c.u[at])
+    rep = compare(part, z[at])
+    assert rep.hard == 0, rep.first_hard
+
+
+@pytest.mark.parametrize("K", [50, 112, 208])
+def test_any_offsets_stay_in_bounds(K, programs, tmp_path):
+    """Offsets that are no offsets (unordered, negative, past N): some document
+    is drawn from, and nothing outside the arrays is touched."""
+    N, M = 64 * 7 + 9, 30
+    c = make_random(N, M, 37, K, seed=K, alpha=0.5, beta=0.5)
+    g = np.random.Generator(np.random.PCG64(K))
+    for kind in range(6):
+        off = [np.full(M + 1, 2 ** 62), np.full(M + 1, -2 ** 62), np.full(M + 1, N),
+               g.integers(-5 * N, 5 * N, M + 1), g.permutation(doc_offsets(c.doc_id, M)),
+               np.arange(M, -1, -1) * (N // M)][kind].astype(np.int64)
+        z = draw(programs[0], c, shape_of(N, M, K), tmp_path, "docs", off)
+        assert z.min() >= 0 and z.max() < K
