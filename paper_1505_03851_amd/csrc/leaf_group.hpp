@@ -407,11 +407,13 @@ __device__ __forceinline__ void group_reload(GroupFound<H> &f, const Table &th_t
   }
 }
 
-// Topic of padded index i >= 0 (the first quad's empty components hold a draw
-// only by rounding: its last topic).
+// Topic of padded index i.  The first quad's empty components hold a draw only
+// by rounding: its last topic.  The empty leaves before it (i < 0) hold none,
+// unless u or a weight is negative, which is no draw at all: topic 0, so that
+// what is stored always indexes a topic.
 template <bool PAD>
 __device__ __forceinline__ int group_topic(int i, int drop) {
-  return PAD ? max(i - drop, min(i, kLeaf - 1 - drop)) : i;
+  return PAD ? max(max(i - drop, min(i, kLeaf - 1 - drop)), 0) : i;
 }
 
 // The topic of a found token: the first of its leaf's L topics whose running

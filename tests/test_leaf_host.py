@@ -141,3 +141,20 @@ def test_any_offsets_stay_in_bounds(K, programs, tmp_path):
                np.arange(M, -1, -1) * (N // M)][kind].astype(np.int64)
         z = draw(programs[0], c, shape_of(N, M, K), tmp_path, "docs", off)
         assert z.min() >= 0 and z.max() < K
+
+
+@pytest.mark.parametrize("K", [5, 12, 20, 50, 112, 131, 208, 300, 500])
+def test_any_weights_and_uniforms_give_topics(K, programs, tmp_path):
+    """Uniforms below 0, above 1 and NaN, weights below 0, infinite and NaN: the
+    draw has no meaning, but it is a topic (one that indexes theta and phi)."""
+    N, M = 64 * 4, 6
+    c = make_random(N, M, 37, K, seed=K, alpha=0.5, beta=0.5)
+    u, theta, phi = c.u.copy(), c.theta.copy(), c.phi.copy()
+    u[::5], u[1::7], u[2::9], u[3::11] = -0.5, np.nan, 1.5, np.inf
+    theta[1, ::3], theta[2, ::5], theta[3, K // 2], theta[4] = -theta[1, ::3], np.nan, np.inf, 0
+    phi[::7, 0] = np.inf
+    for kw in (dict(u=u), dict(theta=theta), dict(theta=-c.theta), dict(u=u, theta=theta, phi=phi)):
+        bad = dataclasses.replace(c, **kw)
+        for program in programs:
+            z = draw(program, bad, shape_of(N, M, K), tmp_path)
+            assert z.min() >= 0 and z.max() < K
