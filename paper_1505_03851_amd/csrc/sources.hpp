@@ -39,17 +39,18 @@ struct DocSource {
   }
 
   // The same over [0, M - 1] from a guess g: steps of 1, 2, 4, ... away from g
-  // bracket the answer, then bisection (a few probes when g is close).
+  // bracket the answer, then bisection (a few probes when g is close).  (Upwards
+  // lo + step may pass 2^31 where M comes close to it: unsigned.)
   __device__ __forceinline__ int search_from(int64_t t, int g) const {
     int lo, hi;
     if (offsets[g] <= t) {
       lo = g;
-      int step = 1;
-      while (lo + step <= M - 1 && offsets[lo + step] <= t) {
-        lo += step;
+      uint32_t step = 1;
+      while ((uint32_t)lo + step <= (uint32_t)(M - 1) && offsets[(uint32_t)lo + step] <= t) {
+        lo = (int)((uint32_t)lo + step);
         step *= 2;
       }
-      hi = lo + step <= M - 1 ? lo + step - 1 : M - 1;
+      hi = (uint32_t)lo + step <= (uint32_t)(M - 1) ? (int)((uint32_t)lo + step - 1u) : M - 1;
     } else {
       hi = g - 1;
       int step = 1;
@@ -85,12 +86,14 @@ struct DocSource {
   // takes the square root again, where doubling steps from it and the bisection
   // back took some 16 dependent loads.  Measured on MI355X on the paper-shaped
   // corpus: K = 32 38.6 -> 33.7 us, K = 208 135.3 -> 132.9; where the guess is
-  // right at once (equal lengths, K = 64 on 1M tokens) 15.3 -> 15.6.
+  // right or nearly so at once, 1M tokens at K = 64 pay for the moves: documents
+  // of 128 tokens 15.0 -> 15.3 us, of Poisson lengths 16.8 -> 17.1.  (One
+  // division: the second took 0.15 us of a draw at K = 16.)
   __device__ __forceinline__ int wave_doc(int64_t n, int64_t first, int64_t last) const {
     if (ids) return ids[n];
-    int g = (int)((double)first * (double)M / (double)(N > 0 ? N : 1));
-    g = g < 0 ? 0 : (g > M - 1 ? M - 1 : g);
     const double rate = (double)M / (double)(N > 0 ? N : 1);
+    int g = (int)((double)first * rate);
+    g = g < 0 ? 0 : (g > M - 1 ? M - 1 : g);
     for (int i = 0; i < 2; ++i) {
       const double move = (double)(first - offsets[g]) * rate;
       if (move > -2.0 && move < 3.0) break;  // (near: the search's first steps)

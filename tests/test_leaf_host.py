@@ -158,3 +158,21 @@ def test_any_weights_and_uniforms_give_topics(K, programs, tmp_path):
         for program in programs:
             z = draw(program, bad, shape_of(N, M, K), tmp_path)
             assert z.min() >= 0 and z.max() < K
+
+
+@pytest.mark.parametrize("M", [1, 100, 2 ** 30 + 12345, 1_900_000_000, 2 ** 31 - 1])
+def test_document_search_among_very_many_documents(M, tmp_path):
+    """Every token in the last of up to 2^31 - 1 documents: the search's steps
+    double up to the number of documents and stay inside them."""
+    if CLANG is None:
+        pytest.skip("no clang++")
+    exe = str(tmp_path / "doc_search")
+    subprocess.run([CLANG, "-x", "c++", "-std=c++17", "-O1", "-w",
+                    "-I", os.path.join(HERE, "leaf_host"),
+                    "-I", os.path.join(ROOT, "paper_1505_03851_amd", "csrc"),
+                    os.path.join(HERE, "leaf_host", "doc_search.cpp"), "-o", exe], check=True)
+    N = 1 << 20
+    at = [0, 64, N // 64, N // 16, N // 8, N // 5, N // 2, N - 64]
+    run = subprocess.run([exe, str(M), str(N), *map(str, at)], stdout=subprocess.PIPE, text=True)
+    assert run.returncode == 0, (run.returncode, run.stdout)
+    assert run.stdout.split() == [str(M - 1)] * (2 * len(at))
