@@ -108,13 +108,19 @@ bool long_docs(int64_t N, int32_t M) { return N >= 128 * (int64_t)M; }
 
 // Where the kernel looks for scattered documents (spread_draw), and log2 of the
 // tokens of a wavefront's share: documents as ids, theta past an XCD's 4 MiB of
-// L2, and tokens enough that every eighth wavefront's windows fill the chip.
-// Measured on MI355X: with theta of 4 MiB at 1M tokens 63 -> 75 us, of 8 MiB 85
-// -> 83, of 16 MiB 189 -> 139.  Shares of 2^11 (four windows of 64 on average):
-// 142 us at 2M tokens, K = 128; of 2^10 235 (a last window that is mostly
-// empty), of 2^12 153 (too few wavefronts; at 1M tokens 207 against 139).
+// L2, tokens enough that every eighth wavefront's windows fill the chip, and
+// enough of them per document that an XCD reads a row again before it has lost
+// it.  Measured on MI355X: with theta of 4 MiB at 1M tokens 63 -> 75 us, of 8 MiB
+// 85 -> 83, of 16 MiB 189 -> 139; 2M tokens, without -> with, at 64 tokens per
+// document 131 -> 132 (K = 80), 195 -> 167 (128), 411 -> 345 (256), at 40 144 ->
+// 144, 205 -> 195, 417 -> 395, at 30 150 -> 158, 210 -> 215, 424 -> 417, at 10 162
+// -> 199, 222 -> 262, 432 -> 474.  Shares of 2^11 (four windows of 64 on
+// average): 142 us at 2M tokens, K = 128; of 2^10 235 (a last window that is
+// mostly empty), of 2^12 153 (too few wavefronts; at 1M tokens 207 against 139).
 int spread_for(const DocSource &d, int64_t N, int32_t M, int32_t K) {
-  return d.ids && N >= (1 << 20) && (int64_t)M * K * 4 >= (6 << 20) ? 11 : 0;
+  const bool pays = d.ids && N >= (1 << 20) && (int64_t)M * K * 4 >= (6 << 20) &&
+                    N >= 40 * (int64_t)M;
+  return pays ? 11 : 0;
 }
 
 template <int G, int H, int C, int WPEU, bool KEEP>

@@ -114,6 +114,9 @@ constexpr bool kSpread = G >= 32 && H == 1;
 constexpr int kSpreadClasses = 8;
 constexpr int kSpreadBatch = 4;
 constexpr int kSpreadRing = (kSpreadBatch + 1) * kWave;  // listed tokens, 16 bits each
+constexpr int kSpreadNear = 16;   // documents apart that count as near
+constexpr int kSpreadFalls = 24;  // of 64 tokens, far falls of ordered ones at most
+constexpr int kSpreadShare = 2;   // of 64 tokens, those of one class's document at most
 template <int G, int H>
 constexpr int group_lds_bytes() {
   constexpr bool lds = kGroupLast<G, H, false, kGroupOne> == kKeepInLds;
@@ -692,6 +695,47 @@ __device__ __forceinline__ GroupLeaf<H> group_leaf(int K, int r) {
   return l;
 }
 
+// Whether a stretch's documents are scattered, from its first 64 tokens' (d: this
+// lane's token's): they fall far at two tokens of five (shuffled ones at every
+// other).  Short documents in order change at every token but never fall, and
+// the documents of a word, where tokens stand word by word, fall once a word:
+// listed by class, such tokens took 1.2-1.4 times the plain draw's time (2M
+// tokens, one per document, K = 100 ... 256) and 1.1-1.35 times (word by word, K =
+// 100 ... 160).  Nor do shuffled tokens fall that often where one document has
+// half of them, for which the plain draw is the faster one too.
+__device__ __forceinline__ bool scattered(int d) {
+  const int p = __builtin_amdgcn_update_dpp(d, d, 0x138, 0xF, 0xF, false);
+  const bool fall = d < p && (uint32_t)p - (uint32_t)d > (uint32_t)kSpreadNear;
+  return __builtin_popcountll(__builtin_amdgcn_ballot_w64(fall)) > kSpreadFalls;
+}
+
+// Up to two documents that more than kSpreadShare of those 64 tokens share (-1:
+// none).  Their tokens go to all classes by turns: one class, and so one XCD,
+// would otherwise draw a large document alone (20% of shuffled tokens in one
+// document: 1.2-1.8 times the plain draw's time, by turns 0.8-1).  Ten bits of a
+// hash tell documents apart: three of 64 agree by chance in one stretch of 25,
+// which does no harm.
+struct LargeDocs {
+  int d0, d1;
+};
+__device__ __forceinline__ LargeDocs large_docs(int d) {
+  const uint32_t h = (uint32_t)d * 2654435761u;
+  uint64_t same = ~0ull;  // the lanes of this lane's document
+#pragma unroll
+  for (int b = 22; b < 32; ++b) {
+    const bool bit = (h >> b) & 1u;
+    const uint64_t set = __builtin_amdgcn_ballot_w64(bit);
+    same &= bit ? set : ~set;
+  }
+  const uint64_t large = __builtin_amdgcn_ballot_w64(__builtin_popcountll(same) > kSpreadShare);
+  LargeDocs l{-1, -1};
+  if (large == 0) return l;
+  l.d0 = __builtin_amdgcn_readlane(d, __builtin_ctzll(large));
+  const uint64_t rest = large & ~__builtin_amdgcn_ballot_w64(d == l.d0);
+  if (rest) l.d1 = __builtin_amdgcn_readlane(d, __builtin_ctzll(rest));
+  return l;
+}
+
 // Tokens whose documents are scattered (shuffled tokens): theta rows, like phi
 // rows, then come from all over their table in every XCD, and misses past L2
 // bound the draw.  Eight workgroups, one per XCD (workgroup b runs on XCD b
@@ -707,8 +751,9 @@ template <int G, int H, int C, bool KEEP, bool PAD>
 __device__ __forceinline__ void spread_draw(const Table &th_t, const Table &ph_t,
                                             const int32_t *ids, const int32_t *word_id,
                                             const UniformSource &u, int64_t first, int tokens,
-                                            uint32_t cls, const GroupLeaf<H> &leaf, float *sums,
-                                            f4 *stage, uint16_t *ring, int32_t *z) {
+                                            uint32_t cls, LargeDocs large,
+                                            const GroupLeaf<H> &leaf, float *sums, f4 *stage,
+                                            uint16_t *ring, int32_t *z) {
   const int lane = lane_id(), gbase = lane & ~(G - 1);
   const uint64_t below = (1ull << lane) - 1ull;
   constexpr int step = kSpreadBatch * kWave;
@@ -728,7 +773,10 @@ __device__ __forceinline__ void spread_draw(const Table &th_t, const Table &ph_t
 #pragma unroll
       for (int i = 0; i < kSpreadBatch; ++i) {
         const int at = from + i * kWave + lane;
-        const bool mine = at < tokens && ((uint32_t)doc[i] * 2654435761u) >> 29 == cls;
+        uint32_t c = ((uint32_t)doc[i] * 2654435761u) >> 29;
+        if (large.d0 >= 0 && (doc[i] == large.d0 || doc[i] == large.d1))
+          c = (uint32_t)at % kSpreadClasses;
+        const bool mine = at < tokens && c == cls;
         const uint64_t picks = __builtin_amdgcn_ballot_w64(mine);
         if (mine) ring[have + __builtin_popcountll(picks & below)] = (uint16_t)at;
         have += __builtin_popcountll(picks);
@@ -784,8 +832,8 @@ void leaf_group_kernel(const float *__restrict__ theta, const float *__restrict_
   constexpr int CA = K16 ? (PAD ? 2 : 4) : (G == kWave && H == 1 ? C / 2 : C);
   if constexpr (kSpread<G, H>) {
     // spread: log2 of the tokens per wavefront's share of a stretch (0: never).
-    // A stretch whose first 64 tokens change document more than every other
-    // token is drawn by its first eight workgroups; the others are done.
+    // A stretch of scattered documents is drawn by eight of its workgroups; the
+    // others are done.
     const int64_t stretch = (int64_t)kWavesPerBlock << spread;
     const int shift = spread ? spread - 6 : 0;  // log2 of a stretch's workgroups
     const uint32_t index = blockIdx.x >> shift;
@@ -793,8 +841,7 @@ void leaf_group_kernel(const float *__restrict__ theta, const float *__restrict_
     // (a last, incomplete stretch may have fewer than eight workgroups)
     if (spread && s0 + stretch <= N) {
       const int d = docs.ids[s0 + lane];
-      const int p = __builtin_amdgcn_update_dpp(d, d, 0x138, 0xF, 0xF, false);
-      if (__builtin_popcountll(__builtin_amdgcn_ballot_w64(d != p)) > kWave / 2) {
+      if (scattered(d)) {
         // (a stretch's eight by turns: an XCD's CUs get workgroups round robin)
         const uint32_t part = blockIdx.x & ((1u << shift) - 1u);
         const uint32_t turns = (1u << shift) / kSpreadClasses;
@@ -804,9 +851,9 @@ void leaf_group_kernel(const float *__restrict__ theta, const float *__restrict_
         constexpr int CS = G == 32 && !KEEP && !PAD ? 2 : CA;
         spread_draw<G, H, CS, KEEP, PAD>(
             make_table(theta, theta_extent, K), make_table(phi, phi_extent, K), docs.ids + lo,
-            word_id + lo, u, lo, 1 << spread, part % kSpreadClasses, group_leaf<G, H, PAD>(K, r),
-            sums, stage, reinterpret_cast<uint16_t *>(stage + kMaxGroupRuns<G> * H * kWave),
-            z + lo);
+            word_id + lo, u, lo, 1 << spread, part % kSpreadClasses, large_docs(d),
+            group_leaf<G, H, PAD>(K, r), sums, stage,
+            reinterpret_cast<uint16_t *>(stage + kMaxGroupRuns<G> * H * kWave), z + lo);
         return;
       }
     }

@@ -3,11 +3,11 @@
 // only the running wavefront's region is accessible), table loads by emu (a
 // load must stay inside its row).
 //
-//   leaf_host INPUT OUTPUT G H C KEEP TOKENS SPREAD FIRST STEP
+//   leaf_host INPUT OUTPUT G H C KEEP SPREAD FIRST STEP
 //
 // INPUT: int64 N, M, V, K, form (0 doc ids, 1 offsets), then theta, phi, doc_id
 // or offsets, word_id and u.  Workgroups FIRST, FIRST + STEP, ... and the last
-// one are run; OUTPUT gets z (-1: not drawn).
+// one are run (STEP 0: FIRST alone); OUTPUT gets z (-1: not drawn).
 #include "hip/hip_runtime.h"
 
 #include <sanitizer/asan_interface.h>
@@ -44,7 +44,12 @@ void run(const Input &in) {
   const int64_t per = kWavesPerBlock * kWave;
   const int64_t blocks = (in.N + per - 1) / per;
   emu::grid_dim.x = (unsigned)blocks;
-  for (int64_t b = in.first; b < blocks; b = (b + in.step < blocks || b == blocks - 1) ? b + in.step : blocks - 1) {
+  std::vector<int64_t> run_these{in.first};
+  if (in.step > 0) {
+    for (int64_t b = in.first + in.step; b < blocks - 1; b += in.step) run_these.push_back(b);
+    if (in.first < blocks - 1) run_these.push_back(blocks - 1);
+  }
+  for (const int64_t b : run_these) {
     emu::block_idx.x = (unsigned)b;
     for (int w = 0; w < kWavesPerBlock; ++w) {
       char *base = reinterpret_cast<char *>(lds);

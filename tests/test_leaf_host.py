@@ -105,6 +105,46 @@ def test_scattered_documents_in_bounds(K, M, programs, tmp_path):
     assert rep.hard == 0, rep.first_hard
 
 
+@pytest.mark.parametrize("kind,share", [
+    ("shuffled", (0.08, 0.2)), ("one token each", None), ("two tokens each", None),
+    ("one token each, backwards", None), ("by word", None), ("a document of 20%", (0.08, 0.2)),
+    ("a document of 60%", None), ("two documents of 15%", (0.08, 0.2))])
+def test_which_tokens_are_drawn_by_document_class(kind, share, programs, tmp_path):
+    """Only scattered documents: not short ones in order, whose theta rows have no
+    other reader, nor tokens word by word, nor those most of which are one
+    document's; and each class gets about an eighth of the tokens, whatever the
+    largest documents' shares.  (Every workgroup is run on
+    its own: it draws its own 128 tokens, or a class's of half the stretch.)"""
+    N, K = 4096, 66  # one stretch, 32 workgroups
+    g = np.random.Generator(np.random.PCG64(5))
+    M = {"one token": N, "two tokens": N // 2}.get(" ".join(kind.split()[:2]), 7000)
+    d = np.arange(N) * M // N
+    if kind == "one token each, backwards":
+        d = d[::-1]
+    elif kind == "by word":  # ascending in each of 20 words
+        d = np.sort(g.integers(0, M, (20, N // 20 + 1)), axis=1).ravel()[:N]
+    elif not kind.startswith(("one", "two tokens")):
+        d = g.permutation(d)
+        r = g.random(N)
+        if kind.startswith("a document"):
+            d[r < int(kind.split()[3][:-1]) / 100] = 11
+        elif kind.startswith("two documents"):
+            d[r < 0.3] = 11
+            d[r < 0.15] = 6000
+    c = make_random(64, 1, 50, K, seed=1)
+    c = dataclasses.replace(c, theta=np.tile(c.theta, (M, 1)), doc_id=d.astype(np.int32),
+                            word_id=g.integers(0, 50, N, dtype=np.int32),
+                            u=g.random(N, dtype=np.float32))
+    drawn = [draw(programs[0], c, shape_of(N, M, K), tmp_path, spread=11, first=b, step=0) >= 0
+             for b in range(N // 128)]
+    if share is None:
+        for b, got in enumerate(drawn):
+            assert got[128 * b:128 * (b + 1)].all() and got.sum() == 128, b
+    else:
+        of = np.array([got.sum() for got in drawn if got.any()]) / N
+        assert len(of) == 8 and of.min() > share[0] and of.max() < share[1], of
+
+
 @pytest.mark.parametrize("K", [48, 112, 208, 300])
 def test_a_large_ragged_corpus_in_bounds(K, programs, tmp_path):
     """Documents as offsets over six million tokens of lognormal lengths, empty

@@ -51,7 +51,11 @@ def test_tiny_uniforms_behind_empty_components(K):
 
 @pytest.mark.parametrize("N,M,K", [((1 << 20), 16000, 128), ((1 << 20) + 4095, 24000, 101),
                                    ((1 << 20) + 77, 7000, 256), ((1 << 20) + 4096, 9000, 190),
-                                   ((1 << 20) + 1, 30000, 66)])
+                                   ((1 << 20) + 1, 30000, 66),
+                                   # 40 tokens per document and more: listed by class; 128:
+                                   # 32-lane groups that keep their sums, full and padded rows
+                                   ((1 << 20) + 1, 25000, 66), (1 << 21, 16384, 128),
+                                   (2200000, 17000, 101)])
 @pytest.mark.parametrize("order", ["shuffled", "partly"])
 def test_scattered_documents(N, M, K, order):
     """Tokens in no document order, with theta past an XCD's L2: stretches of
