@@ -37,8 +37,8 @@ bool half_tail_for(int32_t K) {
   return nb >= 2 && nb <= LDA_HALF_MAX_BLOCKS;
 }
 
-dim3 wave_grid(int64_t N, int wpb = kWavesPerBlock) {
-  const int64_t waves = (N + kWave - 1) / kWave;
+dim3 wave_grid(int64_t N, int wpb = kWavesPerBlock, int tokens = kWave) {
+  const int64_t waves = (N + tokens - 1) / tokens;
   return dim3((unsigned)((waves + wpb - 1) / wpb));
 }
 
@@ -123,7 +123,25 @@ int spread_for(const DocSource &d, int64_t N, int32_t M, int32_t K) {
   return pays ? 11 : 0;
 }
 
-template <int G, int H, int C, int WPEU, bool KEEP>
+// Whether 64-lane groups draw 16 tokens per wavefront (one tile) instead of 64:
+// where wavefronts of 64 would be about one per SIMD (1,024) or fewer, a
+// wavefront's chain of four tiles is the whole launch; and with 8-topic leaves,
+// of which a SIMD holds three wavefronts, where their second round would be a
+// rest.  Measured on MI355X, 64 -> 16 tokens (documents of 128 tokens to 3, and
+// shuffled): 65,536 tokens K = 208 7.4-10.3 -> 7.2-8.0 us, K = 300 9.7-13.5 ->
+// 8.5-13.1; 98,304 at K = 300 10.8-17.4 -> 10.6-16.8; 4,096 at K = 448 7.9-10.1 ->
+// 7.2-7.6; 229,376 at K = 300 21.6-37.9 -> 20.9-33.9.  Elsewhere more wavefronts
+// only cost: 131,072 tokens at K = 208 8.0-14.1 -> 8.5-14.1, at K = 300 12.2-21.9
+// -> 13.5-21.4; 1M at K = 300 (documents of 128) 74.0 -> 81.7.
+template <int H>
+bool fewer_tokens(int64_t N) {
+  const int64_t waves = (N + kWave - 1) / kWave, simds = 1024;
+  if (H == 1) return waves <= simds;
+  const int64_t round = LDA_LEAF8_WAVES_PER_EU * simds;
+  return waves <= round / 2 || (waves > round && waves < 2 * round);
+}
+
+template <int G, int H, int C, int WPEU, bool KEEP, int TOK = kWave>
 void launch_groups_as(const float *theta, const float *phi, DocSource d, const int32_t *wd,
                       UniformSource u, int32_t *z, int64_t N, int32_t M, int32_t V, int32_t K,
                       hipStream_t s) {
@@ -132,11 +150,13 @@ void launch_groups_as(const float *theta, const float *phi, DocSource d, const i
   const size_t lds = (size_t)kWavesPerBlock * group_lds_bytes<G, H>();
   const int spread = kSpread<G, H> ? spread_for(d, N, M, K) : 0;
   if (K == kLeaf * H * G)
-    leaf_group_kernel<G, H, C, WPEU, KEEP, false><<<wave_grid(N), kBlockThreads, lds, s>>>(
-        theta, phi, d, wd, u, z, N, K, tb, pb, spread);
+    leaf_group_kernel<G, H, C, WPEU, KEEP, false, TOK>
+        <<<wave_grid(N, kWavesPerBlock, TOK), kBlockThreads, lds, s>>>(theta, phi, d, wd, u, z, N,
+                                                                       K, tb, pb, spread);
   else
-    leaf_group_kernel<G, H, C, WPEU, KEEP, true><<<wave_grid(N), kBlockThreads, lds, s>>>(
-        theta, phi, d, wd, u, z, N, K, tb, pb, spread);
+    leaf_group_kernel<G, H, C, WPEU, KEEP, true, TOK>
+        <<<wave_grid(N, kWavesPerBlock, TOK), kBlockThreads, lds, s>>>(theta, phi, d, wd, u, z, N,
+                                                                       K, tb, pb, spread);
 }
 
 // Launch shapes by group and leaf (tuning.hpp).
@@ -144,6 +164,14 @@ template <int G, int H>
 void launch_groups(const float *theta, const float *phi, DocSource d, const int32_t *wd,
                    UniformSource u, int32_t *z, int64_t N, int32_t M, int32_t V, int32_t K,
                    hipStream_t s) {
+  if constexpr (G == kWave) {
+    if (fewer_tokens<H>(N)) {
+      launch_groups_as<G, H, (H > 1 ? LDA_LEAF8_WINDOW : LDA_GROUP64_WINDOW),
+                       (H > 1 ? LDA_LEAF8_WAVES_PER_EU : LDA_GROUP64_WAVES_PER_EU), false, 16>(
+          theta, phi, d, wd, u, z, N, M, V, K, s);
+      return;
+    }
+  }
   if constexpr (H > 1) {
     launch_groups_as<G, H, (LDA_LEAF8_WINDOW < G ? LDA_LEAF8_WINDOW : G), LDA_LEAF8_WAVES_PER_EU,
                      false>(theta, phi, d, wd, u, z, N, M, V, K, s);

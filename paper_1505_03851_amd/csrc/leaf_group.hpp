@@ -479,15 +479,16 @@ __device__ __forceinline__ void group_finish_kept(const GroupFound<1> &f,
 
 // The tiles of a wavefront: leaf sums, search and topics of its 64 tokens.
 // voff[h]: byte offset of quad h of this lane's leaf in a row; real[h]: the
-// topics it holds, in its first components (0: front padding).
-template <int G, int H, int C, bool KEEP, int MODE, bool PAD, bool LISTED = false>
+// topics it holds, in its first components (0: front padding).  NK: the tokens
+// of a group (its first NK lanes').
+template <int G, int H, int C, bool KEEP, int MODE, bool PAD, bool LISTED = false, int NK = G>
 __device__ __forceinline__ void group_tiles(const Table &th_t, const Table &ph_t,
                                             const uint32_t (&voff)[H], const int (&real)[H],
                                             const GroupTokens &tok, int gbase, uint64_t gstarts,
                                             float *sums, f4 *stage, int c0, int drop,
                                             int32_t *z) {
   using S = GroupTile<G>;
-  static_assert(G % C == 0, "the window size must divide G");
+  static_assert(NK % C == 0 && NK % S::kLoads == 0, "the window size must divide NK");
   constexpr int LAST = kGroupLast<G, H, KEEP, MODE>;
   constexpr int R = MODE == kGroupRuns ? kMaxGroupRuns<G> : 1;
   const int lane = lane_id(), r = lane & (G - 1);
@@ -598,7 +599,7 @@ __device__ __forceinline__ void group_tiles(const Table &th_t, const Table &ph_t
   f2 *keep2 = reinterpret_cast<f2 *>(sums + kSumFloats<G>);
   float *keep1 = sums + kSumFloats<G> + 2 * kWave * (G + 1);
 #pragma unroll
-  for (int k = 0; k < G; ++k) {
+  for (int k = 0; k < NK; ++k) {
     Leaf<H> tv;
     if constexpr (MODE == kGroupAny) {
       tv = mask(twin[k % C]);
@@ -638,12 +639,12 @@ __device__ __forceinline__ void group_tiles(const Table &th_t, const Table &ph_t
       a[k] = sum;
     else
       put[(k % S::kLoads) * S::kRow] = sum;
-    if (k + C < G) {
+    if (k + C < NK) {
       win[k % C] = ph_leaf(k + C);
       if constexpr (MODE == kGroupAny) twin[k % C] = th_leaf(k + C);
     }
     if constexpr (STAGED)
-      if (k + CT < G) twin[k % CT] = staged(k + CT);
+      if (k + CT < NK) twin[k % CT] = staged(k + CT);
     __builtin_amdgcn_sched_barrier(0);
     if ((k + 1) % S::kLoads == 0) {
       // The tile's search; its reload is in flight while the next tile's
@@ -801,8 +802,9 @@ __device__ __forceinline__ void spread_draw(const Table &th_t, const Table &ph_t
   }
 }
 
-// L = 4 H topics per lane: groups of G lanes cover 4 H G topics.
-template <int G, int H, int C, int WPEU, bool KEEP, bool PAD>
+// L = 4 H topics per lane: groups of G lanes cover 4 H G topics.  A wavefront
+// draws TOK tokens: 64, or for 64-lane groups 16, one tile (fewer_tokens).
+template <int G, int H, int C, int WPEU, bool KEEP, bool PAD, int TOK = kWave>
 __global__ __launch_bounds__(kBlockThreads) __attribute__((amdgpu_waves_per_eu(WPEU)))
 void leaf_group_kernel(const float *__restrict__ theta, const float *__restrict__ phi,
                        DocSource docs, const int32_t *__restrict__ word_id,
@@ -813,14 +815,16 @@ void leaf_group_kernel(const float *__restrict__ theta, const float *__restrict_
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   float *sums = lds + wave * (group_lds_bytes<G, H>() / (int)sizeof(float));
   f4 *stage = reinterpret_cast<f4 *>(sums + kSumFloats<G>);
-  const int64_t first = ((int64_t)blockIdx.x * kWavesPerBlock + wave) * kWave;
+  const int64_t first = ((int64_t)blockIdx.x * kWavesPerBlock + wave) * TOK;
   const int r = lane & (G - 1), gbase = lane & ~(G - 1);
-  // Window of 64 tokens as in butterfly_kernel (N >= 64 here).
-  const int64_t t0 = first + kWave <= N ? first : N - kWave;
+  // Window of TOK tokens as in butterfly_kernel (N >= 64 here); lanes past it
+  // repeat the last token.
+  static_assert(TOK == kWave || (G == kWave && TOK == GroupTile<G>::kTokens), "whole tiles");
+  const int64_t t0 = first + TOK <= N ? first : N - TOK;
   GroupTokens tok;
-  const int64_t n = t0 + lane;
+  const int64_t n = t0 + (TOK == kWave ? lane : min(lane, TOK - 1));
   tok.at = lane;
-  tok.store = n >= first;
+  tok.store = n >= first && lane < TOK;
   int doc = docs.ids ? docs.ids[n] : 0;
   const int word = word_id[n];
   tok.u = u(n);
@@ -830,7 +834,7 @@ void leaf_group_kernel(const float *__restrict__ theta, const float *__restrict_
   constexpr bool K16 = G == 16 && H == 1 && KEEP;
   constexpr int C1 = K16 ? G : C;
   constexpr int CA = K16 ? (PAD ? 2 : 4) : (G == kWave && H == 1 ? C / 2 : C);
-  if constexpr (kSpread<G, H>) {
+  if constexpr (kSpread<G, H> && TOK == kWave) {
     // spread: log2 of the tokens per wavefront's share of a stretch (0: never).
     // A stretch of scattered documents is drawn by eight of its workgroups; the
     // others are done.
@@ -859,7 +863,7 @@ void leaf_group_kernel(const float *__restrict__ theta, const float *__restrict_
     }
   }
   if (first >= N) return;  // whole wavefront past the end
-  if (!docs.ids) doc = docs.wave_doc(n, t0, t0 + kWave - 1);
+  if (!docs.ids) doc = docs.wave_doc(n, t0, t0 + TOK - 1);
   z += t0;
 
   const Table th_t = make_table(theta, theta_extent, K);
@@ -882,15 +886,16 @@ void leaf_group_kernel(const float *__restrict__ theta, const float *__restrict_
   for (int g = 0; g < kWave / G; ++g)
     most = max(most, __builtin_popcountll((starts >> (g * G)) & gmask));
 
+  constexpr int NK = TOK == kWave ? G : TOK;  // tokens of a group
   if (most == 0)
-    group_tiles<G, H, C1, KEEP, kGroupOne, PAD>(th_t, ph_t, leaf.voff, leaf.real, tok, gbase, 0,
-                                                sums, stage, leaf.c0, leaf.drop, z);
+    group_tiles<G, H, C1, KEEP, kGroupOne, PAD, false, NK>(
+        th_t, ph_t, leaf.voff, leaf.real, tok, gbase, 0, sums, stage, leaf.c0, leaf.drop, z);
   else if (most < kMaxGroupRuns<G>)
-    group_tiles<G, H, C, KEEP, kGroupRuns, PAD>(th_t, ph_t, leaf.voff, leaf.real, tok, gbase,
-                                                gstarts, sums, stage, leaf.c0, leaf.drop, z);
+    group_tiles<G, H, C, KEEP, kGroupRuns, PAD, false, NK>(
+        th_t, ph_t, leaf.voff, leaf.real, tok, gbase, gstarts, sums, stage, leaf.c0, leaf.drop, z);
   else
-    group_tiles<G, H, CA, KEEP, kGroupAny, PAD>(th_t, ph_t, leaf.voff, leaf.real, tok, gbase, 0,
-                                                sums, stage, leaf.c0, leaf.drop, z);
+    group_tiles<G, H, CA, KEEP, kGroupAny, PAD, false, NK>(
+        th_t, ph_t, leaf.voff, leaf.real, tok, gbase, 0, sums, stage, leaf.c0, leaf.drop, z);
 }
 
 }  // namespace

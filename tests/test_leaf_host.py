@@ -39,16 +39,23 @@ def programs(tmp_path_factory):
 
 
 def shape_of(N, M, K):
-    """(G, H, C, KEEP) of the dispatch."""
+    """(G, H, C, KEEP, TOK) of the dispatch (TOK: of calls of many tokens)."""
     if K > 256:
-        return 64, 2, 4, 0
+        return 64, 2, 4, 0, 64
     if K > 128:
-        return 64, 1, 8, 0
+        return 64, 1, 8, 0, 64
     if K > 64:
-        return (32, 1, 8, 1) if N >= 128 * M else (32, 1, 4, 0)
+        return (32, 1, 8, 1, 64) if N >= 128 * M else (32, 1, 4, 0, 64)
     if K > 32:
-        return 16, 1, 8, 1
-    return (8, 1, 8, 0) if K > 16 else (4, 1, 4, 0)
+        return 16, 1, 8, 1, 64
+    return (8, 1, 8, 0, 64) if K > 16 else (4, 1, 4, 0, 64)
+
+
+def shapes_of(K):
+    if 64 < K <= 128:
+        return (32, 1, 8, 1, 64), (32, 1, 4, 0, 64)
+    full = shape_of(1, 1, K)
+    return (full, full[:4] + (16,)) if full[0] == 64 else (full,)
 
 
 def draw(program, c, shape, tmp, form="ids", offsets=None, spread=0, first=0, step=1):
@@ -75,11 +82,8 @@ def test_every_shape_in_bounds(K, programs, tmp_path):
     for N, M, order in ((64 * 5 + 1, 2, "sequential"), (64 * 5 + 63, 12, "ragged"),
                         (64 * 2, 60, "ragged"), (64 * 3 + 17, 40, "shuffled"), (64, 1, "single")):
         c = make_random(N, M, 37, K, seed=K, alpha=0.5, beta=0.5, doc_order=order)
-        shapes = {shape_of(N, M, K)}
-        if 64 < K <= 128:
-            shapes = {(32, 1, 8, 1), (32, 1, 4, 0)}
         for program in programs:
-            for shape in shapes:
+            for shape in shapes_of(K):
                 for form in ("ids",) if order == "shuffled" else ("ids", "docs"):
                     z = draw(program, c, shape, tmp_path, form)
                     rep = compare(c, z)
@@ -91,7 +95,7 @@ def test_eight_topic_leaves_in_bounds(K, programs, tmp_path):
     G = 4 if K <= 32 else 8 if K <= 64 else 16 if K <= 128 else 32
     for N, M, order in ((64 * 3 + 5, 8, "ragged"), (64 * 2 + 17, 40, "shuffled")):
         c = make_random(N, M, 37, K, seed=K, alpha=0.5, beta=0.5, doc_order=order)
-        rep = compare(c, draw(programs[0], c, (G, 2, 4, 0), tmp_path))
+        rep = compare(c, draw(programs[0], c, (G, 2, 4, 0, 64), tmp_path))
         assert rep.hard == 0, rep.first_hard
 
 
@@ -196,8 +200,9 @@ def test_any_weights_and_uniforms_give_topics(K, programs, tmp_path):
     for kw in (dict(u=u), dict(theta=theta), dict(theta=-c.theta), dict(u=u, theta=theta, phi=phi)):
         bad = dataclasses.replace(c, **kw)
         for program in programs:
-            z = draw(program, bad, shape_of(N, M, K), tmp_path)
-            assert z.min() >= 0 and z.max() < K
+            for shape in shapes_of(K):
+                z = draw(program, bad, shape, tmp_path)
+                assert z.min() >= 0 and z.max() < K
 
 
 @pytest.mark.parametrize("M", [1, 100, 2 ** 30 + 12345, 1_900_000_000, 2 ** 31 - 1])

@@ -31,6 +31,20 @@ def test_rows_of_every_width(K):
         assert np.array_equal(z["butterfly"], z["variant-wide"])
 
 
+@pytest.mark.parametrize("K", [130, 256, 257, 512])
+@pytest.mark.parametrize("N", [64, 65, 79, 65536, 65537, 98304, 98305, 196609, 393153])
+def test_few_and_many_tokens_per_wavefront(N, K):
+    """64-lane groups at the edges of the rule that gives a wavefront 16 tokens,
+    and of such a wavefront: every form of the documents."""
+    for M, order in ((max(1, N // 128), "sequential"), (max(1, N // 30), "ragged"),
+                     (50, "shuffled")):
+        c = make_random(N, M, 300, K, seed=K, alpha=0.5, beta=0.5, doc_order=order)
+        dev = to_device(c)
+        for name in ("butterfly", "variant-wide") + (("docs",) if order != "shuffled" else ()):
+            rep = compare(c, run_kernel(name, dev))
+            assert rep.hard == 0, (name, order, rep.first_hard)
+
+
 @pytest.mark.parametrize("K", [5, 18, 35, 66, 131, 259])
 def test_tiny_uniforms_behind_empty_components(K):
     """Stops of 0 and of a few ulps of S, and the largest u, with every second
