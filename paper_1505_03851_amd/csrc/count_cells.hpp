@@ -21,17 +21,27 @@
 // bucket's workgroup.
 // The runs and offsets need 4 bytes per token and 2 per chunk and bucket.
 // They lie in the document table, which is written after them (its rows whole
-// by count_docs_kernel, or cleared and added to by count_kernel): the call
-// overwrites both tables in any case, so it needs no workspace.
+// by count_docs_kernel, or cleared and added to by count_doc_ids_kernel): the
+// call overwrites both tables in any case, so it needs no workspace.
 //
 // Measured on MI355X at 16.8M tokens, K = 1024, V = 100,000: split 122 us (600
 // MB read and written, 5 TB/s: the copy rate), cells 111 us: 52 for reading the
 // pieces (64 bytes each on average), 20 for the table, 40 for the 1.7M single
 // stores.
+//
+// A bucket's table holds 8,192 cells, 2.1M or 4.2M in all.  Where the topics
+// fill more (a sampler's first sweeps over a large corpus: near-uniform topics),
+// tokens that find no slot are added in memory.  Their walk over 32 taken slots
+// cost more than that addition: once one token has been through it, the others
+// of the bucket try four.  16.8M uniform topics (6.6M cells) 692 -> 590 us, 50M
+// (12.4M cells) 1,553 -> 1,058, 7.9M over 256 buckets (2.8M cells) 315 -> 209; over
+// the word index, without the partition, these took 632, 1,325 and 314.
 #pragma once
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "config.hpp"
 #include "counts.hpp"
@@ -44,6 +54,7 @@ constexpr int kCellThreads = 1024;
 constexpr int kCellSlots = 8192;        // hash slots of a bucket (64 KiB of LDS)
 constexpr int kMerges = 4;              // cells merged per 64 entries of a long piece
 constexpr int kCellProbes = 32;         // probes before a token goes to memory
+constexpr int kFullProbes = 4;          // ... once the table is full (a token has)
 constexpr uint32_t kCellMul = 2654435761u;  // odd: a bijection mod 2^32
 
 // Inverse of an odd number mod 2^32 (Newton: each step doubles the bits).
@@ -216,11 +227,12 @@ __global__ __launch_bounds__(kSplitThreads) void count_split_kernel(
 }
 
 // `n` more tokens of the cell with low hash bits `low`: counted in the LDS
-// table from `slot` on, or, where no slot is free within kCellProbes, in
-// memory (true).
+// table from `slot` on, or, where none of PROBES slots takes it, in memory
+// (true).
+template <int PROBES>
 __device__ __forceinline__ bool cell_spills(uint32_t *keys, uint32_t *cnt, uint32_t low,
                                             uint32_t slot, uint32_t n) {
-  for (int probe = 0; probe < kCellProbes; ++probe) {
+  for (int probe = 0; probe < PROBES; ++probe) {
     uint32_t k = __hip_atomic_load(&keys[slot], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     if (k == kCountEmpty) k = atomicCAS(&keys[slot], kCountEmpty, low);
     if (k == kCountEmpty || k == low) {
@@ -261,15 +273,16 @@ void count_cells_kernel(
   const auto cell_of = [&](uint32_t low) {
     return (size_t)(((p << (32 - BITS)) | low) * inverse32(kCellMul));
   };
-  const auto add = [&](uint32_t e) {
-    const uint32_t low = e & S::kLow, n = (e >> (32 - BITS)) + 1u;
-    if (cell_spills(keys, cnt, low, low >> kSlotShift, n)) {
-      atomicAdd(&nwk[cell_of(low)], (int32_t)n);
-      spilled = 1;
-    }
-  };
   // (run positions and offsets are below 2^32: N < 2^31)
-  for (uint32_t g0 = 0; g0 < chunks; g0 += kGroups * kAhead) {
+  const auto pieces = [&](uint32_t g0, auto full) {
+    const auto add = [&](uint32_t e) {
+      const uint32_t low = e & S::kLow, n = (e >> (32 - BITS)) + 1u;
+      if (cell_spills<full.value ? kFullProbes : kCellProbes>(keys, cnt, low, low >> kSlotShift,
+                                                              n)) {
+        atomicAdd(&nwk[cell_of(low)], (int32_t)n);
+        if (!full.value) spilled = 1;
+      }
+    };
     uint32_t from[kAhead], left[kAhead], e[kAhead], seen[kAhead];
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
@@ -301,7 +314,13 @@ void count_cells_kernel(
         // (a piece longer than its lanes)
         for (uint32_t i = S::kLanes; i < left[u]; i += S::kLanes) add(runs[from[u] + i]);
       }
-  }
+  };
+  const auto overflows = [&] {
+    return __hip_atomic_load(&spilled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) != 0;
+  };
+  uint32_t g0 = 0;
+  for (; g0 < chunks && !overflows(); g0 += kGroups * kAhead) pieces(g0, std::false_type());
+  for (; g0 < chunks; g0 += kGroups * kAhead) pieces(g0, std::true_type());
   __syncthreads();
   const bool sum = spilled != 0;
   for (int s = t; s < kCellSlots; s += kCellThreads) {

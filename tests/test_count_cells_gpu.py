@@ -25,6 +25,7 @@ CASES = [
     (7999999, 70000, 30000, 128, "zipf"),
     (8000000, 70000, 30000, 128, "zipf"),
     (8000000 + 8191, 70000, 50000, 512, "flat"),  # tables overflow
+    (6000001, 40000, 60000, 400, "flat"),         # ... the fewer ones of shorter calls
 ]
 
 
