@@ -106,15 +106,17 @@ KERNELS = ("butterfly", "naive", "transposed", "docs", "doc_lanes", "doc_lanes_c
            "count-indexed", "word-index", "sweep")
 
 
-def draw_occupancy(K: int) -> tuple[int, int]:
+def draw_occupancy(K: int, tokens_per_doc: float = 128.0) -> tuple[int, int]:
     """(wavefronts per workgroup, wavefronts per CU) of the kernel
-    lda_draw_butterfly launches for K divisible by 4 (N >= 64), as the
-    compiler's register report for gfx950 gives them: the leaf-group kernel up
-    to K = 256, 2 per workgroup and, per SIMD, 6 for groups of 8 lanes (K <=
-    32), 5 for 16, 4 for 32 and 3 for 64; the leaf-eighths kernel above (4 per
+    lda_draw_butterfly launches for K divisible by 4 on a large corpus, as the
+    compiler's register report for gfx950 gives them.  The leaf-group kernel up
+    to K = 512, 2 per workgroup and, per SIMD, 6 for groups of 4 and 8 lanes (K
+    <= 32), 5 for 16, 4 for 32 on documents of 128 tokens and more, else 5, 4 for
+    64, 3 with 8-topic leaves (K > 256); the leaf-eighths kernel above (4 per
     workgroup and 2 per SIMD up to 1280 topics, then 2 and 4)."""
-    if K <= 256:
-        per_simd = 6 if K <= 32 else 5 if K <= 64 else 4 if K <= 128 else 3
+    if K <= 512:
+        per_simd = (6 if K <= 32 else 5 if K <= 64 else
+                    (4 if tokens_per_doc >= 128 else 5) if K <= 128 else 4 if K <= 256 else 3)
         return 2, 4 * per_simd
     return (4, 8) if K <= 1280 else (2, 16)
 
@@ -152,7 +154,8 @@ def launcher(kernel: str, dev):
         return build_and_draw
     if kernel == "floor":
         from paper_1505_03851_amd import probe
-        window, wpg, wpc = dev.get("floor_cfg") or (16,) + draw_occupancy(th.shape[1])
+        window, wpg, wpc = dev.get("floor_cfg") or (16,) + draw_occupancy(
+            th.shape[1], w.shape[0] / th.shape[0])
         return lambda out, stream: probe.draw_floor(th, ph, d, w, u, out, window=window,
                                                     waves_per_group=wpg, waves_per_cu=wpc,
                                                     stream=stream)
@@ -783,6 +786,13 @@ PROFILE_TARGETS = {
                                             "--steps", "3", "--warmup", "1"]),
     "ccells_K1024": ("count_cells_kernel", ["--only", "count-docs", "--workload", HEADLINE,
                                             "--steps", "3", "--warmup", "1"]),
+    # documents of more tokens than topics: the word table without the partition
+    "count_K64": ("count_kernel", ["--only", "count", "--workload", "corpus1M-K64",
+                                   "--steps", "3", "--warmup", "1"]),
+    "cwords_K64": ("count_words_kernel", ["--only", "count-docs", "--workload", "corpus1M-K64",
+                                          "--steps", "3", "--warmup", "1"]),
+    "cindex_K64": ("count_words_indexed", ["--only", "count-indexed", "--workload",
+                                           "corpus1M-K64", "--steps", "3", "--warmup", "1"]),
     "draw_K256": ("leaf_group_kernel", ["--only", "butterfly", "--workload", SECOND,
                                         "--steps", "3", "--warmup", "1"]),
     "floor_K256": ("floor_kernel", ["--only", "floor", "--floor-config", "16,2,0",
@@ -1047,10 +1057,10 @@ def report_parity(log: str, out_txt: str, command: str) -> int:
     return 0
 
 
-def floor_configs(K: int):
+def floor_configs(K: int, tokens_per_doc: float):
     """Launch shapes of the floor probe tried for K: window 8 or 16, 2 or 4
     wavefronts per workgroup, no occupancy cap or the draw's."""
-    wpg, wpc = draw_occupancy(K)
+    wpg, wpc = draw_occupancy(K, tokens_per_doc)
     return [(w, g, c) for w in (8, 16) for g in (2, 4) for c in (0, wpc)]
 
 
@@ -1058,7 +1068,7 @@ def measure_floor(name: str, c, dev, steps: int, warmup: int) -> dict:
     """The memory-only floor of the draw on this workload: every launch shape
     of ``floor_configs`` timed, the fastest kept."""
     shapes = {}
-    for cfg in floor_configs(c.K):
+    for cfg in floor_configs(c.K, c.N / c.M):
         dev["floor_cfg"] = cfg
         r = measure(name, c, dev, "floor", steps, warmup)
         r.pop("z")

@@ -2,6 +2,7 @@
 roofline divides by, the source hash that decides whether a counter record
 still applies, and the reducer of the GPU tests' parity lines."""
 import os
+import re
 import shutil
 import sys
 from types import SimpleNamespace
@@ -63,3 +64,18 @@ def test_report_parity_keeps_the_named_workloads(tmp_path):
     text = out.read_text()
     assert "corpus16M-K1024 routed philox" in text and "16777216" in text
     assert "random-N5" not in text
+
+
+def test_draw_occupancy_of_the_launch_shapes():
+    # the wavefronts per SIMD that the dispatch's launch shapes ask for
+    with open(os.path.join(bench.CSRC, "draw_dispatch.hpp"), encoding="utf-8") as f:
+        text = f.read()
+    with open(os.path.join(bench.CSRC, "tuning.hpp"), encoding="utf-8") as f:
+        tuning = dict(re.findall(r"#define (LDA_\w+) (\d+)", f.read()))
+    assert bench.draw_occupancy(300) == (2, 4 * int(tuning["LDA_LEAF8_WAVES_PER_EU"]))
+    assert bench.draw_occupancy(208) == (2, 4 * int(tuning["LDA_GROUP64_WAVES_PER_EU"]))
+    keep = re.search(r"launch_groups_as<G, H, 8, (\d), true>\(theta, phi, d, wd, u, z, N, M, V, K, s\);"
+                     r"\s+else\s+launch_groups_as<G, H, 4, (\d), false>", text)
+    assert bench.draw_occupancy(112, 128) == (2, 4 * int(keep[1]))
+    assert bench.draw_occupancy(112, 127.9) == (2, 4 * int(keep[2]))
+    assert bench.draw_occupancy(512)[1] == 12 and bench.draw_occupancy(516) == (4, 8)
