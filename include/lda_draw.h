@@ -360,7 +360,9 @@ int lda_draw_routed_philox(const float *theta, const float *phi, const void *wor
  * table above LDA_MAX_COUNT_TABLE_BYTES (2^32 - 1 cells: cells are addressed
  * by unsigned 32-bit indices) give LDA_ERR_UNSUPPORTED.  Enqueues kernels
  * only; nothing is allocated (from 524,288 tokens the call uses ndk as scratch
- * before it writes it, if ndk has more cells than there are tokens).
+ * before it writes it, if ndk can hold 4 N + 2 c (b + 1) bytes, about 1.032 cells
+ * per token: c chunks of 4,096 tokens in b = 256 buckets, from 8,000,000 tokens of
+ * 8,192 in 512).
  */
 #define LDA_COUNT_MAX_N 2147483647LL
 int lda_count_topics(const int32_t *doc_id, const int32_t *word_id, const int32_t *z,
@@ -415,8 +417,9 @@ int lda_word_index_build(const int32_t *word_id, int64_t N, int32_t V, void *ind
 
 /*
  * lda_count_topics_docs with the word table counted from a word index
- * (lda_word_index_build over the same word_id, N and V).  Calls of at least
- * 524,288 tokens whose ndk has more cells than there are tokens count it as
+ * (lda_word_index_build over the same word_id, N and V).  Calls that
+ * use ndk as scratch (see lda_count_topics: 524,288 tokens and more whose
+ * documents are on average shorter than about K tokens) count it as
  * lda_count_topics_docs does, without the index.  Otherwise the tokens are taken
  * word by word, each workgroup a run of 2,048-position chunks; each cell's
  * tokens are summed in an LDS table, and when the table is written out the

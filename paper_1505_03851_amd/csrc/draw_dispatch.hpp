@@ -100,10 +100,14 @@ bool groups_for(int64_t N, int32_t K) {
 
 // Documents long enough that a 32-lane group's 32 consecutive tokens mostly
 // share one: there the sums are kept in registers (118 VGPRs, 4 wavefronts per
-// SIMD), else more wavefronts run (5 per SIMD).  Measured on MI355X: keeping
-// takes 199 us against 226 at K = 128 on 8M tokens in documents of 128, but
-// 152 against 135 at K = 80 on 6M tokens in documents of 69 on average; with
-// 128 tokens per document about half the groups' pairs lie in one document.
+// SIMD), else more wavefronts run (5 per SIMD).  Measured on MI355X on 4M tokens,
+// not kept -> kept, documents of 64 tokens on average, of 96, 128 and 400: K = 80
+// 88 -> 89 us, 86 -> 86, 85 -> 86, 80 -> 81; K = 112 101 -> 101, 100 -> 96, 98 -> 93,
+// 97 -> 88; K = 128 102 -> 101, 102 -> 98, 102 -> 95, 99 -> 90; with offsets 3-4%
+// less is gained (K = 112 104 -> 108, 101 -> 102, 100 -> 100, 99 -> 96).  Shuffled
+// tokens, whatever the documents' lengths: 0-3% (K = 128 on 2M tokens by document
+// class: 148 -> 142).  The line could lie at 96 with document ids; it stands where
+// neither form loses.
 bool long_docs(int64_t N, int32_t M) { return N >= 128 * (int64_t)M; }
 
 // Where the kernel looks for scattered documents (spread_draw), and log2 of the
@@ -181,8 +185,9 @@ void launch_groups(const float *theta, const float *phi, DocSource d, const int3
   } else if constexpr (G == 32) {
     if (long_docs(N, M))
       launch_groups_as<G, H, 8, 4, true>(theta, phi, d, wd, u, z, N, M, V, K, s);
-    else
-      launch_groups_as<G, H, 4, 5, false>(theta, phi, d, wd, u, z, N, M, V, K, s);
+    else  // (the wide build's 64-bit addresses do not fit 5 wavefronts' registers: padded
+          // rows at 5 spilled, K = 112 on 3M tokens 82.3 us, at 4 77.4)
+      launch_groups_as<G, H, 4, 5 - LDA_WIDE_TABLES, false>(theta, phi, d, wd, u, z, N, M, V, K, s);
   } else if constexpr (G == 16) {
     launch_groups_as<G, H, 8, 5, true>(theta, phi, d, wd, u, z, N, M, V, K, s);
   } else {
@@ -196,17 +201,20 @@ void launch_groups(const float *theta, const float *phi, DocSource d, const int3
 // 50,000): 282 against 350 us at K = 260 (18% with the butterfly search it had
 // before), 347 at 384, 409 against 419 at 448, 470 against 479 at 512; against
 // the one-topic kernel 304 against 380 at K = 301, 491 against 609 at 501.
+// (Shuffled tokens at K = 448, 480 and 512 would be 4-18% faster by the eighths
+// kernel up to 1M tokens, as fast at 2M; documents in order are 3-40% slower
+// there, the shorter the more, and the order is not known on the host.)
 bool leaf8_for(int64_t N, int32_t K) {
   return N >= kWave && K > kLeaf * kWave && K <= LDA_LEAF8_MAX_K && K <= 2 * kLeaf * kWave;
 }
 
-// The eighths kernel takes K divisible by 4 (16-byte leaves) from
-// LDA_EIGHTHS_MIN_K topics to LDA_EIGHTHS_MAX_BLOCKS 256-topic blocks, for
-// N >= 64.  Measured on MI355X against the one-topic kernel: 15-30% faster
-// from K = 144 (K = 144 ... 240 on the paper-shaped corpus), 7% at K = 256,
-// 4% at K = 1024, 5% at K = 2048; 3-4% slower at K = 80 and 112, whose
-// padding fills most of the block.  (The dispatch gives K up to 512 to
-// the leaf-group kernel first.)
+// The eighths kernel takes K divisible by 4 (16-byte leaves) up to
+// LDA_EIGHTHS_MAX_BLOCKS blocks, N >= 64.  Measured on MI355X against the
+// one-topic kernel: 4% faster at K = 1024, 5% at K = 2048.  The dispatch gives K
+// up to 512 to the leaf-group kernel first; LDA_EIGHTHS_MIN_K bounds it in builds
+// that lower LDA_GROUP_MAX_K or LDA_LEAF8_MAX_K (there it was 15-30% faster than the
+// one-topic kernel from K = 144, 3-4% slower at K = 80 and 112, whose padding fills
+// most of the block).
 bool eighths_for(int64_t N, int32_t K) {
   return N >= kWave && K % kLeaf == 0 && K >= LDA_EIGHTHS_MIN_K &&
          eighths_blocks(K) <= LDA_EIGHTHS_MAX_BLOCKS;
@@ -228,9 +236,9 @@ void launch_butterfly(const float *theta, const float *phi, DocSource d,
         theta, phi, d, wd, u, z, N, K, tb, pb);
 }
 
-// The leaf-group kernel with groups just wide enough for K: K up to 32, 64,
-// 128, 256 topics take 8, 16, 32, 64 lanes with 4-topic leaves (H = 1), half
-// as many with 8-topic leaves (H = 2).
+// The leaf-group kernel with groups just wide enough for K: K up to 16, 32, 64,
+// 128, 256 topics take 4, 8, 16, 32, 64 lanes with 4-topic leaves (H = 1), half
+// as many, at least 4, with 8-topic leaves (H = 2).
 template <int H>
 void dispatch_groups(const float *theta, const float *phi, DocSource d, const int32_t *word_id,
                      UniformSource u, int32_t *z, int64_t N, int32_t M, int32_t V, int32_t K,

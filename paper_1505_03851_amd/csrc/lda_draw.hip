@@ -661,8 +661,9 @@ bool launch_cells(const int32_t *doc_id, const int32_t *word_id, const int32_t *
 }
 
 // The word table by partition of its cells (count_cells.hpp), with ndk as
-// scratch; false (nothing launched) where ndk cannot hold it (about as many
-// tokens as cells of ndk, or more) or N is too small to pay.  doc_id null:
+// scratch; false (nothing launched) where ndk cannot hold it (CellSplit::bytes:
+// fewer than 1.032 cells of ndk per token, documents longer than about K) or N is
+// too small to pay.  doc_id null:
 // offsets form.  Measured on MI355X, whole calls, before -> now: with document
 // ids 72 -> 51 us on 1M tokens at K = 256 and 1,086 -> 610 on 16.8M at K =
 // 1024; with offsets 145 -> 54 on the paper-shaped corpus at K = 112, 347 ->

@@ -6,9 +6,9 @@
 namespace LDA_NS {
 namespace {
 
-// Leaf kernel with 32-topic prefix rows (K divisible by 4, from
-// LDA_EIGHTHS_MIN_K topics to LDA_EIGHTHS_MAX_BLOCKS 256-topic blocks,
-// N >= 64; when K is not a multiple of 256 the first block begins with
+// Leaf kernel with 32-topic prefix rows (K divisible by 4 up to
+// LDA_EIGHTHS_MAX_BLOCKS 256-topic blocks, N >= 64; the dispatch gives K up to 512
+// to the leaf groups first; when K is not a multiple of 256 the first block begins with
 // 256 - K mod 256 empty topics, as the remnant block of butterfly_kernel).
 //
 // The sweep reads every token's phi row with 16-byte loads: lane l takes the

@@ -80,9 +80,10 @@
 #ifndef LDA_LEAF8_WAVES_PER_EU
 #define LDA_LEAF8_WAVES_PER_EU 3
 #endif
-//   LDA_EIGHTHS_MIN_K         smallest K it takes (K divisible by 4; the first
-//                             block is padded with empty topics up to a
-//                             multiple of 256).
+//   LDA_EIGHTHS_MIN_K         smallest K it takes where the leaf groups leave it
+//                             (LDA_GROUP_MAX_K or LDA_LEAF8_MAX_K lowered; K
+//                             divisible by 4; the first block is padded with
+//                             empty topics up to a multiple of 256).
 #ifndef LDA_EIGHTHS_MIN_K
 #define LDA_EIGHTHS_MIN_K 132
 #endif

@@ -75,7 +75,7 @@ def test_draw_occupancy_of_the_launch_shapes():
     assert bench.draw_occupancy(300) == (2, 4 * int(tuning["LDA_LEAF8_WAVES_PER_EU"]))
     assert bench.draw_occupancy(208) == (2, 4 * int(tuning["LDA_GROUP64_WAVES_PER_EU"]))
     keep = re.search(r"launch_groups_as<G, H, 8, (\d), true>\(theta, phi, d, wd, u, z, N, M, V, K, s\);"
-                     r"\s+else\s+launch_groups_as<G, H, 4, (\d), false>", text)
+                     r"\s+else.*?launch_groups_as<G, H, 4, (\d)(?: - LDA_WIDE_TABLES)?, false>", text, re.S)
     assert bench.draw_occupancy(112, 128) == (2, 4 * int(keep[1]))
     assert bench.draw_occupancy(112, 127.9) == (2, 4 * int(keep[2]))
     assert bench.draw_occupancy(512)[1] == 12 and bench.draw_occupancy(516) == (4, 8)
